@@ -7,8 +7,8 @@
  * (the procedure closing Sec. IV):
  *   1. every particle transforms the same minibatch of m source points
  *      (SGD-ICP minibatch, Sec. III-B),
- *   2. each transformed point is matched to its nearest reference point by
- *      brute force (Eq. 1),
+ *   2. each transformed point is matched to its nearest reference point
+ *      (Eq. 1, exactly: the brute-force answer),
  *   3. each particle takes the mean point-to-point gradient (Eqs. 4-5),
  *   4. the particles are coupled by the Stein direction of Eq. 16 with an
  *      RBF translation kernel and the wrapped-angle rotation kernel of
@@ -58,7 +58,10 @@ extern "C" {
  * by a power of two and split into two FP16 parts (FP16's 11-bit significand
  * carries in two parts what BF16 needs three for): one matrix product per
  * block of references instead of two, with an error bound of the same size.
- * All three modes return the same answers. */
+ * All three modes return the same answers. A context indexes its references
+ * at init (clouds up to 2^24 points) and then searches the index, in every
+ * mode and with the same answers, unless stein_icp_set_nn_tiling asks for the
+ * mode's brute-force search. */
 enum { STEIN_ICP_NN_FP32 = 0, STEIN_ICP_NN_BF16_RERANK = 1, STEIN_ICP_NN_F16_RERANK = 2 };
 /* Update rule: Adam on -phi (Sec. V), or theta += lr * phi (Eq. 12). */
 enum { STEIN_ICP_OPT_ADAM = 0, STEIN_ICP_OPT_SGD = 1 };
@@ -106,7 +109,7 @@ typedef struct stein_icp_config {
     double prior_kappa_rot[3];  /* >= 0 */
     int64_t n_scale;         /* N multiplying the mean gradient (Eq. 16); 0 = source size */
     int32_t use_graph;       /* 1: stein_icp_step replays captured hipGraphs */
-    int32_t autotune;        /* 1: time candidate NN tile shapes at init and keep the best */
+    int32_t autotune;        /* 1: time candidate NN work shapes at init and keep the best */
     int32_t metric;          /* STEIN_ICP_METRIC_* */
     int32_t normal_k;        /* neighbours per normal (PLANE), 3 <= normal_k <= 32 */
 } stein_icp_config;
@@ -192,8 +195,9 @@ int stein_icp_get_diagnostics(const stein_icp_ctx *ctx, double *gbar, double *ph
 /* Number of pairs, particles and minibatch size of a context. */
 int stein_icp_shape(const stein_icp_ctx *ctx, int32_t *n_pairs, int32_t *K, int32_t *m);
 
-/* Nearest-neighbour work shape of the context: FP32 queries per lane,
- * wavefronts per workgroup, references per workgroup chunk and chunks (of
+/* Nearest-neighbour work shape of the context (of its brute-force search;
+ * the indexed search holds one chunk of all references): FP32 queries per
+ * lane, wavefronts per workgroup, references per workgroup chunk and chunks (of
  * pair 0), persistence (0: one workgroup per work item; n: n workgroups per
  * compute unit walking the work table of all pairs), and the mean time in ms
  * of one NN + gradient launch pair measured by the autotuner (0 if not
@@ -201,7 +205,8 @@ int stein_icp_shape(const stein_icp_ctx *ctx, int32_t *n_pairs, int32_t *K, int3
 int stein_icp_nn_tiling(const stein_icp_ctx *ctx, int32_t *queries_per_lane, int32_t *waves,
                         int32_t *chunk, int32_t *chunks, int32_t *persist, double *tuned_ms);
 
-/* Force the nearest-neighbour work shape: queries_per_lane in {1, 2, 4},
+/* Force the brute-force search of the context's mode, in this shape, in place
+ * of the indexed one: queries_per_lane in {1, 2, 4},
  * waves in {4, 8, 16}, chunk a positive multiple of 32 references (capped
  * at each pair's padded reference count), persist in [0, 64] as above. The
  * BF16 screen takes 1 or 2 queries per lane, and 4 or 8 waves with 2. The
@@ -231,7 +236,8 @@ int stein_icp_time_nn(stein_icp_ctx *ctx, int32_t n_launches, double *ms_per_lau
  * neighbour launch of the context (iterations, profiled and timed launches):
  * *certificates: screen certificates evaluated -- one per real query, chunk,
  *   lane half (two) and wavefront holding blocks of the chunk (Eq. 1 is
- *   proved exact for each);
+ *   proved exact for each); with the indexed search one per real query,
+ *   none of which can fail;
  * *rescans: those that failed and were searched again in FP32.
  * Either output may be NULL. Blocking (synchronises `hip_stream`). */
 int stein_icp_nn_rescans(const stein_icp_ctx *ctx, int64_t *rescans, int64_t *certificates,

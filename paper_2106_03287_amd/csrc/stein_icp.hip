@@ -20,6 +20,7 @@
 #include "nn_bf16_launch.h"
 #include "normals.hpp"
 #include "prep.hpp"
+#include "ref_index.hpp"
 #include "svgd.hpp"
 
 using namespace sicp;
@@ -46,18 +47,18 @@ inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 // Centre of the BF16 screen (the reference centroid, rounded to FP32) in
 // c0[0..2] and, in c0[3], an upper bound of the norms of the centred
 // references as the kernels form them (FP32 differences), which sizes the
-// screen's error bound.
-void bf16_centre(const float* xyz, int64_t n, PairDesc& pd)
+// screen's error bound. `stride` floats from one point to the next.
+void bf16_centre(const float* xyz, int64_t stride, int64_t n, PairDesc& pd)
 {
     double acc[3] = {0, 0, 0};
     for (int64_t i = 0; i < n; ++i)
-        for (int d = 0; d < 3; ++d) acc[d] += xyz[3 * i + d];
+        for (int d = 0; d < 3; ++d) acc[d] += xyz[stride * i + d];
     for (int d = 0; d < 3; ++d) pd.c0[d] = std::isfinite(acc[d]) ? (float)(acc[d] / n) : 0.0f;
     double r2 = 0.0;
     for (int64_t i = 0; i < n; ++i) {
         double q = 0.0;
         for (int d = 0; d < 3; ++d) {
-            const float c = xyz[3 * i + d] - pd.c0[d];   // FP32, as in the kernels
+            const float c = xyz[stride * i + d] - pd.c0[d];   // FP32, as in the kernels
             q += (double)c * c;
         }
         r2 = std::max(r2, q);
@@ -120,6 +121,7 @@ struct Tiling {
     int q = 2;                   // queries per lane
     int w = 4;                   // wavefronts per workgroup
     int persist = 0;             // 0: one workgroup per item; n: n workgroups per CU, grid-stride
+    int run = 1;                 // indexed search: queries a group of lanes takes in turn
     std::vector<int32_t> chunk;  // per pair, references per chunk
 };
 
@@ -139,6 +141,15 @@ int32_t default_chunk(int64_t n_ref_pad, int64_t nq, int q, int64_t pairs)
     return (int32_t)round_up(ceil_div(n_ref_pad, c), 4 * kTile);
 }
 
+// Queries in turn per group of lanes of the indexed search.
+int default_index_run(int64_t queries)
+{
+    const int64_t groups = 32768;
+    int run = 1;
+    while (run < 8 && queries / (2 * run) >= groups) run *= 2;
+    return run;
+}
+
 Tiling default_tiling(const std::vector<PairDesc>& pd, int64_t nq)
 {
     Tiling t;
@@ -152,9 +163,12 @@ Tiling default_tiling(const std::vector<PairDesc>& pd, int64_t nq)
 struct TuneKey {
     int32_t P;
     int64_t nq, refs;
+    bool indexed;
     bool operator<(const TuneKey& o) const
     {
-        return P != o.P ? P < o.P : (nq != o.nq ? nq < o.nq : refs < o.refs);
+        if (P != o.P) return P < o.P;
+        if (nq != o.nq) return nq < o.nq;
+        return refs != o.refs ? refs < o.refs : indexed < o.indexed;
     }
 };
 std::map<TuneKey, std::pair<Tiling, double>> g_tuned;
@@ -176,6 +190,7 @@ struct stein_icp_ctx {
     PairDesc* d_pairs = nullptr;
     std::vector<PairDesc> groups;   // NN groups (runs of consecutive pairs on one packed reference)
     PairDesc* d_groups = nullptr;
+    PairDesc* d_upairs = nullptr;   // the pairs that own their reference
     float4* src4 = nullptr;
     float4* ref4 = nullptr;
     int32_t* sched = nullptr;
@@ -188,7 +203,13 @@ struct stein_icp_ctx {
     int parity = 0;
     Pose* pose = nullptr;
     float4* queries = nullptr;   // FP32 queries of the coming iteration, K*m per pair
-    uint4* apack = nullptr;      // BF16 reference fragments (BF16 screen only)
+    uint4* apack = nullptr;      // BF16 reference fragments (brute-force screens only; an allocation of its own)
+    // the indexed search, which replaces the brute-force ones of every
+    // nn_mode until stein_icp_set_nn_tiling asks for a brute-force shape
+    bool indexed = false;
+    IndexDesc* d_idesc = nullptr;   // one per packed reference
+    int32_t* d_cloud = nullptr;     // index of each pair's packed reference
+    float4* nodes = nullptr;
     int32_t* match = nullptr;
     double* nrm = nullptr;       // point-to-plane: (n, 0) per packed reference, FP64
     double* dscr = nullptr;
@@ -235,10 +256,12 @@ int fused_bandwidth_form(int K)
     return bandwidth_role_lds_bytes(K, kKeysInLds) <= kFusedBandwidthLds ? kKeysInLds : kKeysInGlobal;
 }
 
-bool fused_bandwidth(const stein_icp_config& c, int64_t pairs)
+bool fused_bandwidth(const stein_icp_ctx* ctx)
 {
+    const stein_icp_config& c = ctx->cfg;
+    const int64_t pairs = ctx->P;
     const int K = c.num_particles;
-    return is_screen(c.nn_mode) && !const_bandwidth(c) &&
+    return is_screen(c.nn_mode) && !ctx->indexed && !const_bandwidth(c) &&
            bandwidth_role_lds_bytes(K, fused_bandwidth_form(K)) <= kFusedBandwidthLds &&
            pairs * K <= 2 * (int64_t)g_num_cus;
 }
@@ -365,6 +388,16 @@ void build_work(stein_icp_ctx* c)
 {
     c->work.clear();
     c->groups.clear();
+    if (c->indexed) {   // one key per query
+        for (int32_t p = 0; p < c->P; ++p) {
+            PairDesc& pd = c->pairs[p];
+            pd.chunk = (int32_t)std::min<int64_t>(pd.n_ref_pad, INT32_MAX);
+            pd.chunks = 1;
+            pd.part_off = pd.q_off;
+            pd.part_stride = c->nq;
+        }
+        return;
+    }
     for (int32_t p = 0; p < c->P; ++p) {
         PairDesc& pd = c->pairs[p];
         pd.chunk = c->tiling.chunk[p];
@@ -407,10 +440,12 @@ void build_work(stein_icp_ctx* c)
 
 // Screen certificates one NN launch evaluates: every real query, for every
 // chunk, once per lane half (two) and per wavefront that holds blocks of the
-// chunk (min(waves, blocks)).
+// chunk (min(waves, blocks)). The indexed search proves each answer once, by
+// its box bounds, and none can fail.
 int64_t certificates_per_launch(const stein_icp_ctx* c)
 {
     if (!is_screen(c->cfg.nn_mode)) return 0;
+    if (c->indexed) return (int64_t)c->P * c->nq;
     int64_t n = 0;
     for (const auto& g : c->groups)
         for (int32_t ch = 0; ch < g.chunks; ++ch) {
@@ -423,6 +458,7 @@ int64_t certificates_per_launch(const stein_icp_ctx* c)
 
 int64_t partial_elems(const stein_icp_ctx* c)
 {
+    if (c->indexed) return (int64_t)c->P * c->nq;
     int64_t n = 0;
     for (const auto& g : c->groups) n += (int64_t)g.chunks * g.nq;
     return n;
@@ -441,9 +477,12 @@ int upload_tiling(stein_icp_ctx* c, hipStream_t s)
         return fail(STEIN_ICP_E_NOMEM, "device allocation of the NN work table failed");
     }
     HIP_TRY(hipMemcpyAsync(c->d_pairs, c->pairs.data(), sizeof(PairDesc) * c->P, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->d_groups, c->groups.data(), sizeof(PairDesc) * c->groups.size(),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->d_work, c->work.data(), sizeof(WorkItem) * c->work.size(), hipMemcpyHostToDevice, s));
+    if (!c->indexed) {
+        HIP_TRY(hipMemcpyAsync(c->d_groups, c->groups.data(), sizeof(PairDesc) * c->groups.size(),
+                               hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync(c->d_work, c->work.data(), sizeof(WorkItem) * c->work.size(), hipMemcpyHostToDevice,
+                               s));
+    }
     HIP_TRY(hipStreamSynchronize(s));
     for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);
     c->graphs.clear();
@@ -499,6 +538,21 @@ hipError_t enqueue_queries(const stein_icp_ctx* c, hipStream_t s)
 hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
 {
     if (stage == 0) {
+        if (c->indexed) {
+            IndexSearchArgs a{};
+            a.desc = c->d_idesc;
+            a.cloud = c->d_cloud;
+            a.nodes = c->nodes;
+            a.ref4 = c->ref4;
+            a.queries = c->queries;
+            a.keys = c->partial;
+            a.K = c->K;
+            a.m = c->m;
+            a.run = c->tiling.run;
+            const int64_t blocks = ceil_div(c->nq, (int64_t)a.run * (kIndexThreads / kFan));
+            hipLaunchKernelGGL(index_nn_kernel, dim3((unsigned)blocks, (unsigned)c->P), dim3(kIndexThreads), 0, s, a);
+            return hipGetLastError();
+        }
         if (is_screen(c->cfg.nn_mode)) {
             NNBf16Args b{};
             b.work = c->d_work;
@@ -508,7 +562,7 @@ hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
             b.queries = c->queries;
             b.partial = c->partial;
             b.rescans = c->rescans;
-            if (fused_bandwidth(c->cfg, c->P)) {
+            if (fused_bandwidth(c)) {
                 b.bw = svgd_args(c);
                 b.bw_blocks = 2 * c->P;
                 b.bw_form = fused_bandwidth_form(c->K);
@@ -534,8 +588,8 @@ hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
     g.K = c->K;
     g.m = c->m;
     g.rows = c->rows;
-    g.index_keys = is_screen(c->cfg.nn_mode) ? 1 : 0;
-    const int32_t bw_pairs = const_bandwidth(c->cfg) || fused_bandwidth(c->cfg, c->P) ? 0 : c->P;
+    g.index_keys = c->indexed || is_screen(c->cfg.nn_mode) ? 1 : 0;
+    const int32_t bw_pairs = const_bandwidth(c->cfg) || fused_bandwidth(c) ? 0 : c->P;
     const int64_t blocks = 2 * (int64_t)bw_pairs + ceil_div((int64_t)c->P * c->K, kGradGroups);
     hipLaunchKernelGGL(grad_bandwidth_kernel, dim3((unsigned)blocks), dim3(kSvgdThreads), grad_bw_lds_bytes(c->K), s,
                        g, svgd_args(c), c->P, bw_pairs);
@@ -650,7 +704,7 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
 {
     int64_t refs = 0;
     for (const auto& pd : c->pairs) refs += pd.n_ref_pad;
-    const TuneKey tk{c->P, c->nq, refs};
+    const TuneKey tk{c->P, c->nq, refs, c->indexed};
     auto hit = g_tuned.find(tk);
     if (hit != g_tuned.end()) {
         c->tiling = hit->second.first;
@@ -662,6 +716,45 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
     HIP_TRY(hipEventCreate(&e1));
     double best = 1e30;
     Tiling best_t = c->tiling;
+    // mean time in ms of the candidate's NN and gradient launches
+    auto measure = [&](const Tiling& t, double& out) -> int {
+        c->tiling = t;
+        const int rc = upload_tiling(c, s);
+        if (rc) return rc;
+        HIP_TRY(enqueue_stage(c, 0, s));  // warm-up
+        HIP_TRY(enqueue_stage(c, 1, s));
+        const int reps = 10;
+        HIP_TRY(hipEventRecord(e0, s));
+        for (int r = 0; r < reps; ++r) {
+            HIP_TRY(enqueue_stage(c, 0, s));
+            HIP_TRY(enqueue_stage(c, 1, s));
+        }
+        HIP_TRY(hipEventRecord(e1, s));
+        HIP_TRY(hipEventSynchronize(e1));
+        float ms = 0.f;
+        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+        out = ms / reps;
+        return STEIN_ICP_OK;
+    };
+    if (c->indexed) {
+        for (int run : {1, 2, 4, 8, 16}) {
+            Tiling t = c->tiling;
+            t.run = run;
+            double ms = 0.0;
+            const int rc = measure(t, ms);
+            if (rc) return rc;
+            if (ms < best) {
+                best = ms;
+                best_t = t;
+            }
+        }
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        c->tiling = best_t;
+        c->tuned_ms = best;
+        g_tuned[tk] = {best_t, best};
+        return upload_tiling(c, s);
+    }
     std::set<std::vector<int32_t>> seen;
     const bool bf16 = is_screen(c->cfg.nn_mode);
     for (int q : {1, 2, 4})
@@ -679,23 +772,11 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
                 sig.push_back(q);
                 sig.push_back(w);
                 if (!seen.insert(sig).second) continue;   // same shape as an earlier span
-                c->tiling = t;
-                int rc = upload_tiling(c, s);
+                double ms = 0.0;
+                const int rc = measure(t, ms);
                 if (rc) return rc;
-                HIP_TRY(enqueue_stage(c, 0, s));  // warm-up
-                HIP_TRY(enqueue_stage(c, 1, s));
-                const int reps = 10;
-                HIP_TRY(hipEventRecord(e0, s));
-                for (int r = 0; r < reps; ++r) {
-                    HIP_TRY(enqueue_stage(c, 0, s));
-                    HIP_TRY(enqueue_stage(c, 1, s));
-                }
-                HIP_TRY(hipEventRecord(e1, s));
-                HIP_TRY(hipEventSynchronize(e1));
-                float ms = 0.f;
-                HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (ms / reps < best) {
-                    best = ms / reps;
+                if (ms < best) {
+                    best = ms;
                     best_t = t;
                 }
             }
@@ -703,23 +784,11 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
     for (int per : {1, 2, 4, 8}) {
         Tiling t = best_t;
         t.persist = per;
-        c->tiling = t;
-        int rc = upload_tiling(c, s);
+        double ms = 0.0;
+        const int rc = measure(t, ms);
         if (rc) return rc;
-        HIP_TRY(enqueue_stage(c, 0, s));
-        HIP_TRY(enqueue_stage(c, 1, s));
-        const int reps = 10;
-        HIP_TRY(hipEventRecord(e0, s));
-        for (int r = 0; r < reps; ++r) {
-            HIP_TRY(enqueue_stage(c, 0, s));
-            HIP_TRY(enqueue_stage(c, 1, s));
-        }
-        HIP_TRY(hipEventRecord(e1, s));
-        HIP_TRY(hipEventSynchronize(e1));
-        float ms = 0.f;
-        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-        if (ms / reps < best) {
-            best = ms / reps;
+        if (ms < best) {
+            best = ms;
             best_t = t;
         }
     }
@@ -798,7 +867,99 @@ void free_ctx(stein_icp_ctx* c)
     if (c->arena) (void)hipFree(c->arena);
     if (c->d_work) (void)hipFree(c->d_work);
     if (c->partial) (void)hipFree(c->partial);
+    if (c->apack) (void)hipFree(c->apack);
     delete c;
+}
+
+// Device memory of an index build besides the nodes and the plan.
+struct IndexScratch {
+    size_t plan = 0, split = 0, state = 0, hist = 0;   // bytes
+    explicit IndexScratch(const IndexPlan& pl)
+    {
+        plan = sizeof(IndexDesc) * pl.desc.size() + sizeof(IndexSeg) * pl.seg.size() +
+               sizeof(IndexTile) * (pl.tile.size() + pl.top_tile.size()) + sizeof(IndexChunk) * pl.chunk.size();
+        split = 2 * sizeof(float4) * (size_t)pl.points;
+        state = sizeof(IndexSegState) * pl.seg.size();
+        hist = 4 * (size_t)kSplitBins * pl.seg.size();
+    }
+};
+
+// Upload the plan to `dst` (host copy in `blob`, which must outlive the
+// copy) and enqueue the build. b: ref4, nodes, split, state and hist set,
+// state and hist zeroed on the stream. The descriptors come first in `dst`.
+hipError_t enqueue_index_build(const IndexPlan& pl, std::vector<char>& blob, char* dst, IndexBuildArgs b,
+                               hipStream_t s)
+{
+    blob.clear();
+    auto put = [&](const auto& v) {
+        const size_t o = blob.size();
+        const char* p = (const char*)v.data();
+        blob.insert(blob.end(), p, p + sizeof(v[0]) * v.size());
+        return dst + o;
+    };
+    b.desc = (const IndexDesc*)put(pl.desc);
+    b.seg = (const IndexSeg*)put(pl.seg);
+    b.chunk = (const IndexChunk*)put(pl.chunk);
+    const IndexTile* tile = (const IndexTile*)put(pl.tile);
+    const IndexTile* top = (const IndexTile*)put(pl.top_tile);
+    hipError_t e = hipMemcpyAsync(dst, blob.data(), blob.size(), hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return e;
+    if (!pl.top_tile.empty()) {
+        b.tile = top;
+        hipLaunchKernelGGL(index_bounds_kernel, dim3((unsigned)pl.top_tile.size()), dim3(kSplitThreads), 0, s, b);
+    }
+    for (size_t r = 0; r + 1 < pl.round_tile.size(); ++r) {
+        const dim3 grid((unsigned)(pl.round_tile[r + 1] - pl.round_tile[r]));
+        b.tile = tile + pl.round_tile[r];
+        b.round = (int32_t)r;
+        hipLaunchKernelGGL(index_hist_kernel, grid, dim3(kSplitThreads), 0, s, b);
+        hipLaunchKernelGGL(index_split_kernel, grid, dim3(kSplitThreads), 0, s, b);
+    }
+    hipLaunchKernelGGL(index_chunk_kernel, dim3((unsigned)pl.chunk.size()), dim3(kChunkThreads), 0, s, b);
+    if (pl.uppers)
+        hipLaunchKernelGGL(index_upper_kernel, dim3((unsigned)pl.desc.size()), dim3(kIndexThreads), 0, s, b);
+    return hipGetLastError();
+}
+
+// The brute-force screens' centres and reference fragments, from the packed
+// references (blocking). The caller uploads the pair table again.
+int build_screen(stein_icp_ctx* c, hipStream_t s)
+{
+    std::vector<float4> h;
+    std::vector<PairDesc> uref;
+    std::map<int64_t, int32_t> owner;   // by ref_off: the pair that packed the cloud
+    int64_t apack_n = 0, maxblk = 0;
+    for (int32_t p = 0; p < c->P; ++p) {
+        PairDesc& pd = c->pairs[p];
+        const auto it = owner.find(pd.ref_off);
+        if (it != owner.end()) {
+            const PairDesc& o = c->pairs[it->second];
+            for (int i = 0; i < 4; ++i) pd.c0[i] = o.c0[i];
+            pd.sexp = o.sexp;
+            pd.apack_off = o.apack_off;
+            continue;
+        }
+        owner[pd.ref_off] = p;
+        h.resize((size_t)pd.n_ref);
+        HIP_TRY(hipMemcpyAsync(h.data(), c->ref4 + pd.ref_off, sizeof(float4) * (size_t)pd.n_ref,
+                               hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        bf16_centre(&h[0].x, 4, pd.n_ref, pd);
+        pd.apack_off = apack_n;
+        apack_n += 4 * pd.n_ref_pad;
+        maxblk = std::max<int64_t>(maxblk, pd.n_ref_pad / kRefPad);
+        uref.push_back(pd);
+    }
+    if (hipMalloc(&c->apack, sizeof(uint4) * (size_t)apack_n) != hipSuccess) {
+        (void)hipGetLastError();
+        c->apack = nullptr;
+        return fail(STEIN_ICP_E_NOMEM, "device allocation of the screen's fragments failed");
+    }
+    HIP_TRY(hipMemcpyAsync(c->d_upairs, uref.data(), sizeof(PairDesc) * uref.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(launch_pack_bf16(c->d_upairs, (int32_t)uref.size(), maxblk, c->ref4, c->apack,
+                             screen_fmt(c->cfg.nn_mode), s));
+    HIP_TRY(hipStreamSynchronize(s));
+    return STEIN_ICP_OK;
 }
 
 int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const float* const* src,
@@ -866,6 +1027,7 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     }
     c->tiling = default_tiling(c->pairs, nq);
     if (is_screen(cfg->nn_mode) && c->tiling.q > 2) c->tiling.q = 2;
+    c->tiling.run = default_index_run((int64_t)P * nq);
     {
         // the attribute is a per-kernel ceiling shared by every context: use
         // the largest any particle count needs (the launch sizes the rest)
@@ -874,29 +1036,24 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         HIP_TRY(hipFuncSetAttribute((const void*)grad_bandwidth_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)most));
     }
-    const bool bf16 = is_screen(cfg->nn_mode);
-    int64_t apack_n = 0;
-    if (bf16) {
-        std::vector<float> h;
-        for (int32_t p = 0; p < P; ++p) {
-            PairDesc& pd = c->pairs[p];
-            if (own_ref[p] != p) {
-                const PairDesc& o = c->pairs[own_ref[p]];
-                for (int i = 0; i < 4; ++i) pd.c0[i] = o.c0[i];
-                pd.sexp = o.sexp;
-                pd.apack_off = o.apack_off;
-                continue;
-            }
-            h.resize((size_t)pd.n_ref * 3);
-            if (hipMemcpy(h.data(), ref[p], 12 * (size_t)pd.n_ref, hipMemcpyDeviceToHost) != hipSuccess) {
-                delete c;
-                return fail(STEIN_ICP_E_DEVICE, "reading the reference cloud for its centroid failed");
-            }
-            bf16_centre(h.data(), pd.n_ref, pd);
-            pd.apack_off = apack_n;
-            apack_n += 4 * pd.n_ref_pad;
+    std::vector<PairDesc> uref;   // one descriptor per packed reference
+    std::vector<int32_t> cloud(P);
+    for (int32_t p = 0; p < P; ++p) {
+        if (own_ref[p] == p) {
+            cloud[p] = (int32_t)uref.size();
+            uref.push_back(c->pairs[p]);
+        } else {
+            cloud[p] = cloud[own_ref[p]];
         }
     }
+    IndexPlan plan;
+    {
+        std::vector<std::pair<int64_t, int64_t>> clouds;
+        for (const auto& pd : uref) clouds.push_back({pd.ref_off, pd.n_ref});
+        c->indexed = index_plan(clouds, plan);
+        if (!c->indexed) plan = IndexPlan();
+    }
+    const IndexScratch scr(plan);
     const int64_t PK6 = (int64_t)P * K * 6;
     const int64_t npairs2 = K >= 2 ? (int64_t)K * (K - 1) : 1;
     size_t off = 0;
@@ -917,7 +1074,9 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     const size_t o_step = take(8 * (size_t)P), o_stepn = take(8 * (size_t)P);
     const size_t o_pose = take(sizeof(Pose) * (size_t)P * K);
     const size_t o_queries = take(sizeof(float4) * (size_t)P * nq);
-    const size_t o_apack = take(sizeof(uint4) * (size_t)std::max<int64_t>(apack_n, 1));
+    const size_t o_nodes = take(sizeof(float4) * (size_t)plan.nodes), o_split = take(scr.split);
+    const size_t o_plan = take(scr.plan), o_state = take(scr.state), o_hist = take(scr.hist);
+    const size_t o_cloud = take(4 * (size_t)P);
     const size_t o_match = take(4 * (size_t)P * nq);
     const bool plane = cfg->metric == STEIN_ICP_METRIC_PLANE;
     const size_t o_nrm = take(plane ? 32 * (size_t)ro : 32);
@@ -946,7 +1105,10 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     c->parity = 0;
     c->pose = (Pose*)(c->arena + o_pose);
     c->queries = (float4*)(c->arena + o_queries);
-    c->apack = (uint4*)(c->arena + o_apack);
+    c->nodes = (float4*)(c->arena + o_nodes);
+    c->d_idesc = (IndexDesc*)(c->arena + o_plan);
+    c->d_cloud = (int32_t*)(c->arena + o_cloud);
+    c->d_upairs = (PairDesc*)(c->arena + o_upairs);
     c->match = (int32_t*)(c->arena + o_match);
     c->nrm = (double*)(c->arena + o_nrm);
     c->dscr = (double*)(c->arena + o_dscr);
@@ -1006,18 +1168,18 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     if (hipMemcpyAsync(c->d_pairs, c->pairs.data(), sizeof(PairDesc) * P, hipMemcpyHostToDevice, s) != hipSuccess)
         return bail(fail(STEIN_ICP_E_DEVICE, "pair table upload failed"));
     if (enqueue_queries(c, s) != hipSuccess) return bail(fail(STEIN_ICP_E_DEVICE, "query kernel launch failed"));
-    std::vector<PairDesc> uref;   // one descriptor per packed reference
-    for (int32_t p = 0; p < P; ++p)
-        if (own_ref[p] == p) uref.push_back(c->pairs[p]);
-    if (bf16) {
-        int64_t maxblk = 0;
-        for (const auto& pd : uref) maxblk = std::max<int64_t>(maxblk, pd.n_ref_pad / kRefPad);
-        PairDesc* d_upairs = (PairDesc*)(c->arena + o_upairs);
-        if (hipMemcpyAsync(d_upairs, uref.data(), sizeof(PairDesc) * uref.size(), hipMemcpyHostToDevice, s) !=
-                hipSuccess ||
-            launch_pack_bf16(d_upairs, (int32_t)uref.size(), maxblk, c->ref4, c->apack, screen_fmt(cfg->nn_mode), s) !=
-                hipSuccess)
-            return bail(fail(STEIN_ICP_E_DEVICE, "BF16 packing launch failed"));
+    std::vector<char> blob;
+    if (c->indexed) {
+        IndexBuildArgs b{};
+        b.ref4 = c->ref4;
+        b.nodes = c->nodes;
+        b.split[0] = (float4*)(c->arena + o_split);
+        b.split[1] = b.split[0] + plan.points;
+        b.state = (IndexSegState*)(c->arena + o_state);
+        b.hist = (uint32_t*)(c->arena + o_hist);
+        if (hipMemcpyAsync(c->d_cloud, cloud.data(), 4 * (size_t)P, hipMemcpyHostToDevice, s) != hipSuccess ||
+            enqueue_index_build(plan, blob, c->arena + o_plan, b, s) != hipSuccess)
+            return bail(fail(STEIN_ICP_E_DEVICE, "index build launch failed"));
     }
     int flag = 0;
     if (hipMemcpyAsync(&flag, c->flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -1032,6 +1194,10 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
                          nullptr, c->nrm + 4 * pd.ref_off, 4, nullptr, s);
             if (rc) return bail(rc);
         }
+    }
+    if (is_screen(cfg->nn_mode) && !c->indexed) {
+        rc = build_screen(c, s);
+        if (rc) return bail(rc);
     }
     rc = upload_tiling(c, s);
     if (rc) return bail(rc);
@@ -1253,10 +1419,19 @@ int stein_icp_set_nn_tiling(stein_icp_ctx* ctx, int32_t qpl, int32_t waves, int3
     t.w = waves;
     t.persist = persist;
     for (const auto& pd : ctx->pairs) t.chunk.push_back((int32_t)std::min<int64_t>(chunk, pd.n_ref_pad));
+    if (is_screen(ctx->cfg.nn_mode) && !ctx->apack) {
+        const int rc = build_screen(ctx, (hipStream_t)hip_stream);
+        if (rc) return rc;
+    }
     const Tiling old = ctx->tiling;
+    const bool indexed = ctx->indexed;
     ctx->tiling = t;
+    ctx->indexed = false;   // the caller asks for a brute-force shape
     const int rc = upload_tiling(ctx, (hipStream_t)hip_stream);
-    if (rc) ctx->tiling = old;
+    if (rc) {
+        ctx->tiling = old;
+        ctx->indexed = indexed;
+    }
     return rc;
 }
 
@@ -1359,7 +1534,7 @@ int stein_icp_nn(const float* q_xyz, int64_t nq, const float* ref_xyz, int64_t n
         std::vector<float> h((size_t)n_ref * 3);
         if (hipMemcpy(h.data(), ref_xyz, 12 * (size_t)n_ref, hipMemcpyDeviceToHost) != hipSuccess)
             return fail(STEIN_ICP_E_DEVICE, "reading the reference cloud for its centroid failed");
-        bf16_centre(h.data(), n_ref, pd);
+        bf16_centre(h.data(), 3, n_ref, pd);
         pd.apack_off = 0;
     }
     std::vector<PairDesc> v{pd};
@@ -1448,7 +1623,7 @@ int stein_icp_screen_values(const float* q_xyz, int64_t nq, const float* ref_xyz
     std::vector<float> h((size_t)n_ref * 3);
     if (hipMemcpy(h.data(), ref_xyz, 12 * (size_t)n_ref, hipMemcpyDeviceToHost) != hipSuccess)
         return fail(STEIN_ICP_E_DEVICE, "reading the reference cloud for its centroid failed");
-    bf16_centre(h.data(), n_ref, pd);
+    bf16_centre(h.data(), 3, n_ref, pd);
     if (centre)
         for (int i = 0; i < 4; ++i) centre[i] = pd.c0[i];
     if (scale_exp) *scale_exp = pd.sexp;
