@@ -11,14 +11,13 @@
 // the boxes are. (Morton order needs no splits but took 2 to 3.5 times the
 // blocks per query: 24.9 against 7.3 for the 100,000-point street scan.)
 //
-// Search: kFan lanes share a query, kWave / kFan queries share a wavefront.
-// One step loads the kFan entries of a block, one per lane, forms each lane's
-// squared distance, and descends into the nearest entry that the best
-// distance so far does not exclude; a lane keeps the distances of the levels
-// above in LDS, so that a finished block resumes its parent where it left
-// off. A point is a box without extent, so that points and boxes take one
-// code path and queries of a wavefront that stand at different levels do not
-// diverge.
+// Search: L lanes share a query, kWave / L queries a wavefront. One step takes
+// the kFan entries of a block, kFan / L per lane, forms their squared
+// distances, and descends into the nearest entry that the best distance so
+// far does not exclude; a lane keeps the distances of the levels above in
+// LDS, so that a finished block resumes its parent where it left off. A point
+// is a box without extent, so that points and boxes take one code path and
+// queries of a wavefront that stand at different levels do not diverge.
 //
 // Exactness: the FP32 distance of a point p of a box [lo, hi] is
 // fma(dz, dz, fma(dy, dy, dx dx)) with dx = fl(q - p). Rounding is monotone
@@ -40,7 +39,7 @@
 
 namespace sicp {
 
-constexpr int kFan = 16;                    // entries per block, lanes per query
+constexpr int kFan = 16;                    // entries per block, and points per leaf
 constexpr int kIndexLevels = 8;             // most levels, the points included
 constexpr int kIndexThreads = 256;
 constexpr int kChunk = kFan * kFan * kFan;  // slots a workgroup of the build orders in LDS
@@ -48,7 +47,10 @@ constexpr int kChunkThreads = kChunk / 4;
 constexpr int64_t kIndexMaxRef = (int64_t)1 << 24;   // block numbers and offsets then stay small integers
 
 // One indexed cloud. Offsets are in float4 elements of the context's index
-// array; a point takes one, a box two (lower and upper corner).
+// array. Entries are stored by fours, coordinate by coordinate: a quad of
+// points is x, y, z, original index; a quad of boxes the lower x, y, z and the
+// upper x, y, z.
+constexpr int kPointQuad = 4, kBoxQuad = 6;   // float4 elements
 struct IndexDesc {
     int64_t ref_off;                  // packed references (original order)
     int64_t n;                        // real references
@@ -62,9 +64,9 @@ struct IndexDesc {
 // rounds of splits, each cutting a segment of chunks into up to four parts
 // along its longest side at exact ranks (a histogram of the coordinate, then
 // a partition; points of a bin that holds a cut go to either side of it).
-// Parts are multiples of 16^j chunks, so that a block of any level is a cell
-// of the partition. One workgroup then orders each chunk in LDS and writes
-// its three lower levels; a last launch forms the levels above.
+// Parts are multiples of kFan^j chunks, so that a block of a level above the
+// chunks is (nearly) a cell of the partition. One workgroup then orders each chunk in LDS and writes
+// its boxes; a last launch forms the levels above.
 constexpr int kSplitBins = 2048;
 constexpr int kSplitThreads = 256;
 constexpr int kSplitTile = 8 * kSplitThreads;
@@ -85,7 +87,7 @@ struct IndexTile {
 
 struct IndexChunk {
     int64_t src;                    // first point, in the source array
-    int32_t n, slots;               // points, and slots (a power of two >= n, at least kFan^2)
+    int32_t n, slots;               // points, and slots (a power of two >= n, at least 256)
     int32_t from;                   // source: -1 the packed references, else an array of the split rounds
     int32_t desc, number;           // cloud, and the chunk's number in it
 };
@@ -119,30 +121,31 @@ inline bool index_plan(const std::vector<std::pair<int64_t, int64_t>>& clouds, I
         d.ref_off = cl.first;
         d.n = n;
         const int32_t di = (int32_t)pl.desc.size();
-        auto level = [&](int64_t elements) {
-            d.level_off[d.levels++] = pl.nodes;
+        auto take = [&](int64_t elements) {
+            const int64_t o = pl.nodes;
             pl.nodes += elements;
+            return o;
+        };
+        // points, then boxes until one block holds a level
+        auto levels = [&](int64_t slots) {
+            d.level_off[d.levels++] = take(slots / 4 * kPointQuad);
+            for (int64_t e = slots / kFan;; e = (e + kFan - 1) / kFan) {
+                d.level_off[d.levels++] = take((e + kFan - 1) / kFan * kFan / 4 * kBoxQuad);
+                if (e <= kFan) break;
+            }
         };
         if (n <= kChunk) {
             int32_t slots = kFan * kFan;
             while (slots < n) slots *= 2;
             d.chunks = 1;
-            level(slots);
-            level(2 * slots / kFan);
-            if (slots > kFan * kFan) level(2 * kFan);
+            levels(slots);
             pl.chunk.push_back(IndexChunk{cl.first, (int32_t)n, slots, -1, di, 0});
         } else {
             const int64_t s0 = (n + kChunk - 1) / kChunk;
             const int64_t per = ((n + s0 - 1) / s0 + kFan - 1) / kFan * kFan;
             const int64_t S = (n + per - 1) / per;
             d.chunks = (int32_t)S;
-            level(S * kChunk);
-            level(2 * S * kFan * kFan);
-            level(2 * S * kFan);
-            for (int64_t e = S;; e = (e + kFan - 1) / kFan) {   // entries of the level
-                level(2 * ((e + kFan - 1) / kFan * kFan));
-                if (e <= kFan) break;
-            }
+            levels(S * kChunk);
             pl.uppers = true;
             const int32_t sg = (int32_t)pl.seg.size();
             pl.seg.push_back(IndexSeg{cl.first, pl.points, (int32_t)n, 0, {0, 0, 0}, 0, 0});
@@ -415,6 +418,17 @@ __device__ __forceinline__ uint32_t dpp(uint32_t v)
 // Lane exchanges of reductions over 2, 4, 8 and 16 lanes.
 constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
+// Box number `box` of a level.
+__device__ __forceinline__ void put_box(float4* level, int64_t box, const float (&lo)[3], const float (&hi)[3])
+{
+    float* o = (float*)(level + box / 4 * kBoxQuad) + box % 4;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        o[4 * e] = lo[e];
+        o[12 + 4 * e] = hi[e];
+    }
+}
+
 // LDS written by the wavefront's other lanes may be read after this (the
 // LDS serves a wavefront in order: only the compiler must keep to it).
 __device__ __forceinline__ void wave_sync()
@@ -424,8 +438,8 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Order one chunk and write its points and its three lower box levels (two,
-// or one, where a lone chunk's points need no more). kChunkThreads threads,
+// Order one chunk and write its points and its boxes of 16, 256 and 4096
+// slots, as far as the cloud has those levels. kChunkThreads threads,
 // thread t at slots 4 t .. 4 t + 3; slots past the points are padding, which
 // sorts to the end. A segment of s slots (first the whole chunk) is sorted
 // along its longest side and quartered, down to leaves of kFan slots; keys
@@ -524,7 +538,7 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
         s = s >= 4 * kFan ? s / 4 : s / 2;
     }
     // points; padding copies the first point of its leaf
-    float4* pts = a.nodes + d.level_off[0] + (int64_t)ch.number * kChunk;
+    float* pts = (float*)(a.nodes + d.level_off[0] + (int64_t)ch.number * (kChunk / 4 * kPointQuad));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int at = u * kChunkThreads + tid;
@@ -532,17 +546,24 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
             uint32_t i = key[at] & (kChunk - 1);
             if ((int)i >= ch.n) i = key[at & ~(kFan - 1)] & (kChunk - 1);
             if ((int)i >= ch.n) i = 0;
-            pts[at] = make_float4(xyz[0][i], xyz[1][i], xyz[2][i], __uint_as_float(orig[i]));
+            float* o = pts + 4 * kPointQuad * (at / 4) + at % 4;
+            o[0] = xyz[0][i];
+            o[4] = xyz[1][i];
+            o[8] = xyz[2][i];
+            o[12] = __uint_as_float(orig[i]);
         }
     }
-    // boxes: a leaf is four threads, a box of level 2 a wavefront
-    auto put = [&](int64_t at, const uint32_t (&v)[6]) {
+    // boxes: 16 slots are four threads, 256 a wavefront
+    auto put = [&](int level, int64_t box, const uint32_t (&v)[6]) {
         const float inf = __builtin_inff();
         const bool any = v[0] != 0;   // order bits of a number are above 0
-        a.nodes[at] = any ? make_float4(from_order_bits(~v[3]), from_order_bits(~v[4]), from_order_bits(~v[5]), 0.f)
-                          : make_float4(inf, inf, inf, 0.f);
-        a.nodes[at + 1] = any ? make_float4(from_order_bits(v[0]), from_order_bits(v[1]), from_order_bits(v[2]), 0.f)
-                              : make_float4(-inf, -inf, -inf, 0.f);
+        float lo[3], hi[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            lo[e] = any ? from_order_bits(~v[3 + e]) : inf;
+            hi[e] = any ? from_order_bits(v[e]) : -inf;
+        }
+        put_box(a.nodes + d.level_off[level], box, lo, hi);
     };
     uint32_t v[6];
     slots_box(v);
@@ -551,8 +572,7 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
         v[e] = max(v[e], dpp<kDppXor1>(v[e]));
         v[e] = max(v[e], dpp<kDppXor2>(v[e]));
     }
-    if ((tid & 3) == 0 && 4 * tid < ch.slots)
-        put(d.level_off[1] + 2 * ((int64_t)ch.number * (kFan * kFan) + tid / 4), v);
+    if ((tid & 3) == 0 && 4 * tid < ch.slots) put(1, (int64_t)ch.number * (kFan * kFan) + tid / 4, v);
 #pragma unroll
     for (int e = 0; e < 6; ++e) {
         v[e] = max(v[e], dpp<kDppHalfMirror>(v[e]));
@@ -561,12 +581,12 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
         v[e] = max(v[e], (uint32_t)__shfl_xor((int)v[e], 32));
         if (lane == 0) gbox[e][wave] = v[e];
     }
-    if (lane == 0 && d.levels > 2) put(d.level_off[2] + 2 * ((int64_t)ch.number * kFan + wave), v);
+    if (lane == 0 && d.levels > 2) put(2, (int64_t)ch.number * kFan + wave, v);   // idle wavefronts pad the block
     __syncthreads();
     if (d.levels > 3 && tid == 0) {
         for (int e = 0; e < 6; ++e)
             for (int w = 0; w < kChunkThreads / kWave; ++w) v[e] = max(v[e], gbox[e][w]);
-        put(d.level_off[3] + 2 * (int64_t)ch.number, v);
+        put(3, ch.number, v);
     }
 }
 
@@ -581,22 +601,18 @@ __global__ __launch_bounds__(kIndexThreads) void index_upper_kernel(IndexBuildAr
         const int64_t padded = (real + kFan - 1) / kFan * kFan;
         for (int64_t e = (l == 3 ? real : 0) + threadIdx.x; e < padded; e += kIndexThreads) {
             const float inf = __builtin_inff();
-            float4 lo = make_float4(inf, inf, inf, 0.f), hi = make_float4(-inf, -inf, -inf, 0.f);
-            if (e < real) {
-                const float4* c = a.nodes + d.level_off[l - 1] + 2 * e * kFan;   // padding boxes are empty
-#pragma unroll 4
-                for (int u = 0; u < kFan; ++u) {
-                    const float4 x = c[2 * u], y = c[2 * u + 1];
-                    lo.x = fminf(lo.x, x.x);
-                    lo.y = fminf(lo.y, x.y);
-                    lo.z = fminf(lo.z, x.z);
-                    hi.x = fmaxf(hi.x, y.x);
-                    hi.y = fmaxf(hi.y, y.y);
-                    hi.z = fmaxf(hi.z, y.z);
-                }
+            float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
+            if (e < real) {   // the children are one block; padding boxes are empty
+                const float4* c = a.nodes + d.level_off[l - 1] + e * (kFan / 4 * kBoxQuad);
+                for (int u = 0; u < kFan / 4; ++u)
+#pragma unroll
+                    for (int f = 0; f < 3; ++f) {
+                        const float4 x = c[u * kBoxQuad + f], y = c[u * kBoxQuad + 3 + f];
+                        lo[f] = fminf(lo[f], fminf(fminf(x.x, x.y), fminf(x.z, x.w)));
+                        hi[f] = fmaxf(hi[f], fmaxf(fmaxf(y.x, y.y), fmaxf(y.z, y.w)));
+                    }
             }
-            a.nodes[d.level_off[l] + 2 * e] = lo;
-            a.nodes[d.level_off[l] + 2 * e + 1] = hi;
+            put_box(a.nodes + d.level_off[l], e, lo, hi);
         }
         __threadfence_block();
         __syncthreads();
@@ -605,13 +621,16 @@ __global__ __launch_bounds__(kIndexThreads) void index_upper_kernel(IndexBuildAr
 }
 
 // ------------------------------------------------------------------ search
-// Minimum over the kFan = 16 lanes of a query.
-__device__ __forceinline__ uint32_t fan_min(uint32_t v)
+// Minimum over the L = 4 or 16 lanes of a query.
+template <int L>
+__device__ __forceinline__ uint32_t lanes_min(uint32_t v)
 {
     v = min(v, dpp<kDppXor1>(v));
     v = min(v, dpp<kDppXor2>(v));
-    v = min(v, dpp<kDppHalfMirror>(v));
-    v = min(v, dpp<kDppMirror>(v));
+    if (L == 16) {
+        v = min(v, dpp<kDppHalfMirror>(v));
+        v = min(v, dpp<kDppMirror>(v));
+    }
     return v;
 }
 
@@ -621,132 +640,160 @@ __device__ __forceinline__ uint64_t dpp64(uint64_t v)
     return ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
 }
 
-__device__ __forceinline__ uint64_t fan_min64(uint64_t v)
+template <int L>
+__device__ __forceinline__ uint64_t lanes_min64(uint64_t v)
 {
     auto take = [&](uint64_t o) { v = o < v ? o : v; };
     take(dpp64<kDppXor1>(v));
     take(dpp64<kDppXor2>(v));
-    take(dpp64<kDppHalfMirror>(v));
-    take(dpp64<kDppMirror>(v));
+    if (L == 16) {
+        take(dpp64<kDppHalfMirror>(v));
+        take(dpp64<kDppMirror>(v));
+    }
     return v;
 }
+
+// E consecutive entries of one coordinate row of a quad.
+template <int E>
+struct alignas(4 * E) Row {
+    float v[E];
+};
 
 struct IndexSearchArgs {
     const IndexDesc* desc;    // per cloud
     const int32_t* cloud;     // cloud of each pair (NULL: cloud 0)
     const float4* nodes;
-    const float4* ref4;
     const float4* queries;    // pair p's at p K m: query k m + i
     uint64_t* keys;           // (distance bits, original index), as the queries
     int32_t K, m;
-    int32_t run, pad_;        // consecutive queries per group of lanes
 };
 
 // Key of no match yet: distance infinity, reference 0 (what the brute-force
 // search returns where no distance is finite).
 constexpr uint64_t kIndexNoMatch = 0x7f80000000000000ull;
 
-// grid (ceil(K m / run / (kIndexThreads / kFan)), pairs). A group of kFan
-// lanes takes `run` queries in turn; queries are ordered by minibatch point,
-// then particle, so that the groups of a wavefront and the turns of a group
-// look for (nearly) the same place: they read the same blocks, and the match
-// of one query bounds the next one's search from the start.
-//
-// Bound by the instructions and the load latency of the dependent steps, 5
-// (2,000 references) to 8 (100,000) blocks a query; the whole index stays in
-// L2. Against the brute-force searches, per launch: 300,000 queries x 100,000
-// street references 1,055 -> 112 us (FP16 screen), 30,000 x 20,000 tabletop
-// 34 -> 14 us, 16,247 x 12,345 85 -> 10 us (BF16 screen), 10,000 x 2,000
-// 9.9 -> 9.0 us (FP32); 64 uneven pairs of 30,000 queries 1,114 -> 523 us.
-__global__ __launch_bounds__(kIndexThreads) void index_nn_kernel(IndexSearchArgs a)
+// Threads of a search workgroup: 16 queries. Larger ones hold their slots
+// until the last of more queries ends (4 lanes, street scan: 64 threads 62.6
+// us a launch, 128 65.0, 256 66.6).
+constexpr int search_threads(int lanes) { return 16 * lanes; }
+
+// Dynamic LDS: a thread's remaining distances, per box level.
+template <int L>
+inline size_t index_nn_lds_bytes(int levels)
 {
-    __shared__ uint32_t above[kIndexLevels][kIndexThreads];   // a lane's remaining distances, per level
-    __shared__ int64_t level_off[kIndexLevels];
+    return (size_t)(levels - 1) * search_threads(L) * (kFan / L) * 4;
+}
+
+// grid (ceil(K m / 16), pairs), search_threads(L) threads; dynamic LDS
+// index_nn_lds_bytes<L>(most levels of the clouds). A query to L lanes; the
+// queries are ordered by minibatch point, then particle, so that those of a
+// wavefront look for (nearly) the same place and read the same blocks.
+//
+// Bound by the vector instructions and the latency of the dependent steps, 5
+// (2,000 references) to 8 (100,000) a query; the whole index stays in L2.
+// us a launch with 4 and with 16 lanes (what it replaced: the brute-force
+// search of the mode): 300,000 queries of 100,000 street references 63 and 85
+// (1,055), 64 uneven pairs of 30,000 queries 348 and 506 (1,114), 1,000 runs
+// of 300 queries of 20,000 68 and 80 (231), 30,000 of 20,000 tabletop 17.4
+// and 13.9 (34), 16,247 of 12,345 13.1 and 10.2 (85), 10,000 of 2,000 11.8
+// and 9.1 (9.9). Left out after measuring: upper levels staged in LDS
+// (slower throughout: the staging and the occupancy cost more than the
+// loads), a second query in turn per group (street 72 -> 82), fan-out 64 on
+// 16 lanes (tabletop 16.6, street 112) and 4 on one lane (41, 94).
+template <int L>
+__global__ __launch_bounds__(search_threads(L)) void index_nn_kernel(IndexSearchArgs a)
+{
+    constexpr int T = search_threads(L);
+    constexpr int E = kFan / L;                   // entries of a block per lane
+    constexpr uint32_t kInf = 0x7f800000u, kEntry = kFan - 1;
+    extern __shared__ float4 lds4[];
+    Row<E>* above = (Row<E>*)lds4;                // [box level - 1][thread]
+    __shared__ int32_t level_off[kIndexLevels];
     const int tid = threadIdx.x;
     const int64_t p = blockIdx.y;
     const IndexDesc& d = a.desc[a.cloud ? a.cloud[p] : 0];
     const int top = d.levels - 1;
-    if (tid < kIndexLevels) level_off[tid] = d.level_off[tid];
+    const float* __restrict__ nodes = (const float*)(a.nodes + d.level_off[0]);
+    const uint32_t fl = tid & (L - 1);
+    if (tid < kIndexLevels) level_off[tid] = 4 * (int32_t)(d.level_off[tid] - d.level_off[0]);
     __syncthreads();
-    const uint32_t fl = tid & (kFan - 1);
-    const int64_t nq = (int64_t)a.K * a.m;
-    int64_t w = ((int64_t)blockIdx.x * (kIndexThreads / kFan) + tid / kFan) * a.run;
-    const int64_t wend = min(w + a.run, nq);
-    if (w >= wend) return;   // no barrier below
-    const float4* __restrict__ ref4 = a.ref4 + d.ref_off;
-    int32_t k = (int32_t)(w % a.K), i = (int32_t)(w / a.K);
+    const uint32_t nq = (uint32_t)a.K * (uint32_t)a.m;   // at most 2^31
+    const uint32_t w = blockIdx.x * (T / L) + tid / L;
+    if (w >= nq) return;   // whole groups; no barrier below
+    const uint64_t qi = p * (uint64_t)nq + (uint64_t)(w % (uint32_t)a.K) * (uint32_t)a.m + w / (uint32_t)a.K;
+    float4 q = a.queries[qi];
     uint64_t key = kIndexNoMatch;
-    float4 q;
-    uint32_t bound;
-    auto start = [&] {
-        q = a.queries[p * nq + (int64_t)k * a.m + i];
-        // the previous match is a reference like any other: its distance
-        // bounds the search from the start
-        const uint32_t j = (uint32_t)key;
-        const float4 r = ref4[j];
-        const float d0 = dist2_f32(q.x, q.y, q.z, r.x, r.y, r.z);
-        const uint64_t k0 = pack_key(d0, j);
-        key = k0 < kIndexNoMatch ? k0 : kIndexNoMatch;
-        // no distance of a query with a NaN is a number: nothing to search
-        const bool nan = !(q.x == q.x && q.y == q.y && q.z == q.z);
-        bound = nan ? 0u : (uint32_t)(key >> 32);
-        if (nan) q = make_float4(__builtin_inff(), 0.f, 0.f, 0.f);
-    };
-    start();
+    uint32_t bound = kInf;
+    // no distance of a query with a NaN is a number: nothing to search
+    if (!(q.x == q.x && q.y == q.y && q.z == q.z)) q = make_float4(__builtin_inff(), 0.f, 0.f, 0.f);
+    const uint32_t quad0 = fl * E / 4, place = fl * E % 4;
     int level = top;
     uint32_t block = 0;
     for (;;) {
-        // distances of the block's entries
-        const uint32_t e = block * kFan + fl;
+        // this lane's entries of the block, and their distances
         const bool box = level > 0;
-        const float4* src = a.nodes + level_off[level] + (box ? 2 * (int64_t)e : (int64_t)e);
-        const float4 lo = src[0];
-        const float4 hi = src[box ? 1 : 0];
-        uint32_t cur;
-        {
+        const uint32_t quad = block * (kFan / 4) + quad0;
+        const uint32_t at = (uint32_t)level_off[level] + 16 * quad + (box ? 8 * quad : 0) + place;
+        const Row<E>* src = (const Row<E>*)(nodes + at);
+        const Row<E>* up = (const Row<E>*)(nodes + at + (box ? 12 : 0));
+        const Row<E> lx = src[0], ly = src[4 / E], lz = src[8 / E], hx = up[0], hy = up[4 / E], hz = up[8 / E];
+        uint32_t cur[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
 #pragma clang fp contract(off)
-            const float dx = __builtin_fmaxf(__builtin_fmaxf(lo.x - q.x, q.x - hi.x), 0.f);
-            const float dy = __builtin_fmaxf(__builtin_fmaxf(lo.y - q.y, q.y - hi.y), 0.f);
-            const float dz = __builtin_fmaxf(__builtin_fmaxf(lo.z - q.z, q.z - hi.z), 0.f);
-            cur = __float_as_uint(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
+            const float dx = __builtin_fmaxf(__builtin_fmaxf(lx.v[u] - q.x, q.x - hx.v[u]), 0.f);
+            const float dy = __builtin_fmaxf(__builtin_fmaxf(ly.v[u] - q.y, q.y - hy.v[u]), 0.f);
+            const float dz = __builtin_fmaxf(__builtin_fmaxf(lz.v[u] - q.z, q.z - hz.v[u]), 0.f);
+            cur[u] = __float_as_uint(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
         }
-        if (!box) {
-            const uint64_t here = ((uint64_t)cur << 32) | __float_as_uint(lo.w);
-            key = here < key ? here : key;
-            bound = min(bound, fan_min(cur));
+        auto least = [&] {
+            uint32_t v = cur[0];
+#pragma unroll
+            for (int u = 1; u < E; ++u) v = min(v, cur[u]);
+            return lanes_min<L>(v);
+        };
+        auto resume = [&](int lv) {   // the distances left of a block of level lv
+            const Row<E> r = above[(lv - 1) * T + tid];
+#pragma unroll
+            for (int u = 0; u < E; ++u) cur[u] = __float_as_uint(r.v[u]);
+        };
+        if (box) {
+            // the low bits make room for the entry (rounded down, so the
+            // bound still holds): the smallest value names the nearest entry
+#pragma unroll
+            for (int u = 0; u < E; ++u) cur[u] = (cur[u] & ~kEntry) | (E * fl + u);
+        } else {
+            const Row<E> id = src[12 / E];
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const uint64_t o = ((uint64_t)cur[u] << 32) | __float_as_uint(id.v[u]);
+                key = o < key ? o : key;
+            }
+            bound = min(bound, least());
             level = 1;
             block /= kFan;
-            cur = above[1][tid];
+            resume(1);
         }
-        // the nearest entry left, of this block or of the levels above: the
-        // low bits of its distance make room for the lane (rounded down, so
-        // the bound still holds)
+        // the nearest entry left, of this block or of the levels above
         uint32_t best;
+        bool open;
         for (;;) {
-            best = fan_min((cur & ~(uint32_t)(kFan - 1)) | fl);
-            if (((best & ~(uint32_t)(kFan - 1)) <= bound && best < 0x7f800000u) || level == top) break;
-            ++level;
+            best = least();
+            open = (best & ~kEntry) <= bound && best < kInf;
+            if (open || level == top) break;
+            resume(++level);
             block /= kFan;
-            cur = above[level][tid];
         }
-        if ((best & ~(uint32_t)(kFan - 1)) <= bound && best < 0x7f800000u) {
-            const uint32_t c = best & (kFan - 1);
-            above[level][tid] = c == fl ? 0x7f800000u : cur;
-            --level;
-            block = block * kFan + c;
-        } else {
-            key = fan_min64(key);
-            if (fl == 0) a.keys[p * nq + (int64_t)k * a.m + i] = key;
-            if (++w >= wend) break;
-            if (++k == a.K) {
-                k = 0;
-                ++i;
-            }
-            start();
-            level = top;
-            block = 0;
-        }
+        if (!open) break;
+        Row<E> r;
+#pragma unroll
+        for (int u = 0; u < E; ++u) r.v[u] = __uint_as_float(cur[u] == best ? kInf : cur[u]);
+        --level;
+        above[level * T + tid] = r;
+        block = block * kFan + (best & kEntry);
     }
+    key = lanes_min64<L>(key);
+    if (fl == 0) a.keys[qi] = key;
 }
 
 }  // namespace sicp

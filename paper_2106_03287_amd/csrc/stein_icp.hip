@@ -121,7 +121,7 @@ struct Tiling {
     int q = 2;                   // queries per lane
     int w = 4;                   // wavefronts per workgroup
     int persist = 0;             // 0: one workgroup per item; n: n workgroups per CU, grid-stride
-    int run = 1;                 // indexed search: queries a group of lanes takes in turn
+    int lanes = 16;              // indexed search: lanes per query
     std::vector<int32_t> chunk;  // per pair, references per chunk
 };
 
@@ -141,14 +141,13 @@ int32_t default_chunk(int64_t n_ref_pad, int64_t nq, int q, int64_t pairs)
     return (int32_t)round_up(ceil_div(n_ref_pad, c), 4 * kTile);
 }
 
-// Queries in turn per group of lanes of the indexed search.
-int default_index_run(int64_t queries)
-{
-    const int64_t groups = 32768;
-    int run = 1;
-    while (run < 8 && queries / (2 * run) >= groups) run *= 2;
-    return run;
-}
+// Lanes per query of the indexed search. Few queries leave the chip to a few
+// wavefronts, whose dependent steps bound the launch: with 16 lanes a
+// wavefront waits for the longest of 4 queries, with 4 of 16. Many queries are
+// bound by the instructions, of which 4 lanes take fewer. 30,000 queries run
+// 25 % faster with 16 lanes, 300,000 26 % faster with 4 (figures at
+// index_nn_kernel).
+int default_index_lanes(int64_t queries) { return queries >= 131072 ? 4 : 16; }
 
 Tiling default_tiling(const std::vector<PairDesc>& pd, int64_t nq)
 {
@@ -207,6 +206,7 @@ struct stein_icp_ctx {
     // the indexed search, which replaces the brute-force ones of every
     // nn_mode until stein_icp_set_nn_tiling asks for a brute-force shape
     bool indexed = false;
+    int index_levels = 2;           // most levels of a cloud
     IndexDesc* d_idesc = nullptr;   // one per packed reference
     int32_t* d_cloud = nullptr;     // index of each pair's packed reference
     float4* nodes = nullptr;
@@ -525,6 +525,14 @@ SvgdArgs svgd_args(const stein_icp_ctx* c)
     return v;
 }
 
+// Indexed search: `lanes` lanes per query, nq queries for each pair.
+void launch_index_nn(int lanes, int levels, int64_t nq, int64_t pairs, const IndexSearchArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)ceil_div(nq, 16), (unsigned)pairs), block(search_threads(lanes));
+    if (lanes == 4) hipLaunchKernelGGL(index_nn_kernel<4>, grid, block, index_nn_lds_bytes<4>(levels), s, a);
+    else hipLaunchKernelGGL(index_nn_kernel<16>, grid, block, index_nn_lds_bytes<16>(levels), s, a);
+}
+
 // Queries of the coming iteration from the current poses and step count.
 hipError_t enqueue_queries(const stein_icp_ctx* c, hipStream_t s)
 {
@@ -543,14 +551,11 @@ hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
             a.desc = c->d_idesc;
             a.cloud = c->d_cloud;
             a.nodes = c->nodes;
-            a.ref4 = c->ref4;
             a.queries = c->queries;
             a.keys = c->partial;
             a.K = c->K;
             a.m = c->m;
-            a.run = c->tiling.run;
-            const int64_t blocks = ceil_div(c->nq, (int64_t)a.run * (kIndexThreads / kFan));
-            hipLaunchKernelGGL(index_nn_kernel, dim3((unsigned)blocks, (unsigned)c->P), dim3(kIndexThreads), 0, s, a);
+            launch_index_nn(c->tiling.lanes, c->index_levels, c->nq, c->P, a, s);
             return hipGetLastError();
         }
         if (is_screen(c->cfg.nn_mode)) {
@@ -737,9 +742,9 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
         return STEIN_ICP_OK;
     };
     if (c->indexed) {
-        for (int run : {1, 2, 4, 8, 16}) {
+        for (int lanes : {4, 16}) {
             Tiling t = c->tiling;
-            t.run = run;
+            t.lanes = lanes;
             double ms = 0.0;
             const int rc = measure(t, ms);
             if (rc) return rc;
@@ -1027,7 +1032,7 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     }
     c->tiling = default_tiling(c->pairs, nq);
     if (is_screen(cfg->nn_mode) && c->tiling.q > 2) c->tiling.q = 2;
-    c->tiling.run = default_index_run((int64_t)P * nq);
+    c->tiling.lanes = default_index_lanes((int64_t)P * nq);
     {
         // the attribute is a per-kernel ceiling shared by every context: use
         // the largest any particle count needs (the launch sizes the rest)
@@ -1052,6 +1057,7 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         for (const auto& pd : uref) clouds.push_back({pd.ref_off, pd.n_ref});
         c->indexed = index_plan(clouds, plan);
         if (!c->indexed) plan = IndexPlan();
+        for (const auto& d : plan.desc) c->index_levels = std::max(c->index_levels, (int)d.levels);
     }
     const IndexScratch scr(plan);
     const int64_t PK6 = (int64_t)P * K * 6;
