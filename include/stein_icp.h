@@ -254,6 +254,7 @@ const char *stein_icp_last_error(void);
  *   q_xyz: device FP32 nq x 3; ref_xyz: device FP32 n_ref x 3;
  *   mode: STEIN_ICP_NN_*; idx: device int32 nq; d2: device FP32 nq (the
  *   FP32 squared distance of the returned index; may be NULL).
+ * Larger searches build an index of the references first (same answers).
  * Allocates and frees its own scratch; blocking. */
 int stein_icp_nn(const float *q_xyz, int64_t nq, const float *ref_xyz, int64_t n_ref,
                  int32_t mode, int32_t *idx, float *d2, void *hip_stream);

@@ -231,7 +231,7 @@ __device__ __forceinline__ void sym3_smallest(double a00, double a01, double a02
     }
 }
 
-// grid: ceil(nq / 256) workgroups of 256 threads, one query each.
+// One query a thread, in workgroups of up to 256.
 template <int KMAX>
 __global__ __launch_bounds__(256) void knn_merge_kernel(KnnMergeArgs a)
 {
@@ -240,7 +240,13 @@ __global__ __launch_bounds__(256) void knn_merge_kernel(KnnMergeArgs a)
     if (qi >= a.nq) return;
     uint64_t b[KMAX];
     topk_init(b, a.k);
-    for (int ch = 0; ch < a.chunks; ++ch) {
+    if (a.chunks == 1) {   // the list as it is
+        const uint64_t* l = a.partial + qi * a.k;
+#pragma unroll
+        for (int s = 0; s < KMAX; ++s)
+            if (s >= KMAX - a.k) b[s] = l[s - (KMAX - a.k)];
+    }
+    for (int ch = 0; ch < a.chunks && a.chunks > 1; ++ch) {
         const uint64_t* l = a.partial + ((int64_t)ch * a.nq + qi) * a.k;
         for (int s = 0; s < a.k; ++s) {
             const uint64_t key = l[s];

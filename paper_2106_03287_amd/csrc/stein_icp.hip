@@ -863,6 +863,46 @@ int run_knn(const float4* q4, int64_t nq, const float4* ref4, int64_t n_ref, int
     return STEIN_ICP_OK;
 }
 
+// Normals of an indexed cloud's references (nrm: 4 doubles per reference).
+// Scratch is allocated here and freed after the stream has drained.
+int run_index_normals(const IndexDesc& d, const IndexDesc* d_desc, const float4* nodes, const float4* ref4, int32_t k,
+                      double* nrm, hipStream_t s)
+{
+    uint64_t* lists = nullptr;
+    if (hipMalloc(&lists, 8 * (size_t)d.n * (size_t)k) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(STEIN_ICP_E_NOMEM, "device allocation for the neighbour lists failed");
+    }
+    IndexKnnArgs a{};
+    a.desc = d_desc;
+    a.nodes = nodes;
+    a.lists = lists;
+    a.k = k;
+    KnnMergeArgs b{};
+    b.partial = lists;
+    b.ref4 = ref4;
+    b.nq = d.n;
+    b.k = k;
+    b.chunks = 1;
+    b.nrm = nrm;
+    b.nrm_stride = 4;
+    const dim3 grid = grid1d(d.level_off[1] - d.level_off[0], 16), block(search_threads(16));
+    const size_t lds = index_nn_lds_bytes<16>(d.levels);
+    if (k <= 16) {
+        hipLaunchKernelGGL(index_knn_kernel<1>, grid, block, lds, s, a);
+        hipLaunchKernelGGL(knn_merge_kernel<16>, grid1d(d.n, 64), dim3(64), 0, s, b);
+    } else {
+        hipLaunchKernelGGL(index_knn_kernel<2>, grid, block, lds, s, a);
+        hipLaunchKernelGGL(knn_merge_kernel<kKnnMax>, grid1d(d.n, 64), dim3(64), 0, s, b);
+    }
+    hipError_t e = hipGetLastError();
+    const hipError_t e2 = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = e2;
+    (void)hipFree(lists);
+    if (e != hipSuccess) return fail(STEIN_ICP_E_DEVICE, std::string("normals: ") + hipGetErrorString(e));
+    return STEIN_ICP_OK;
+}
+
 void free_ctx(stein_icp_ctx* c)
 {
     if (!c) return;
@@ -924,6 +964,103 @@ hipError_t enqueue_index_build(const IndexPlan& pl, std::vector<char>& blob, cha
     if (pl.uppers)
         hipLaunchKernelGGL(index_upper_kernel, dim3((unsigned)pl.desc.size()), dim3(kIndexThreads), 0, s, b);
     return hipGetLastError();
+}
+
+// Device memory of one stand-alone search over an index, from `base` (NULL:
+// sizes only).
+struct IndexedNn {
+    IndexPlan plan;
+    char *zero = nullptr, *d_plan = nullptr;
+    int* flag = nullptr;
+    float4 *q4 = nullptr, *r4 = nullptr;
+    uint64_t* keys = nullptr;
+    IndexBuildArgs b{};
+    int64_t zero_bytes = 0, bytes = 0;
+    bool fits = false;
+
+    IndexedNn(int64_t nq, int64_t n_ref)
+    {
+        fits = index_plan({{0, n_ref}}, plan);
+        if (fits) layout(nullptr, nq, n_ref);
+    }
+    void layout(char* base, int64_t nq, int64_t n_ref)
+    {
+        const IndexScratch scr(plan);
+        int64_t off = 0;
+        const auto take = [&](int64_t n) {
+            char* p = base + off;
+            off += round_up(std::max<int64_t>(n, 1), 256);
+            return p;
+        };
+        zero = take(4);
+        flag = (int*)zero;
+        b.state = (IndexSegState*)take((int64_t)scr.state);
+        b.hist = (uint32_t*)take((int64_t)scr.hist);
+        zero_bytes = off;
+        d_plan = take((int64_t)scr.plan);
+        q4 = (float4*)take(16 * nq);
+        r4 = (float4*)take(16 * n_ref);
+        keys = (uint64_t*)take(8 * nq);
+        b.ref4 = r4;
+        b.nodes = (float4*)take(16 * plan.nodes);
+        b.split[0] = (float4*)take((int64_t)scr.split);
+        b.split[1] = b.split[0] + plan.points;
+        bytes = off;
+    }
+};
+
+// Stand-alone search over an index built for it: enqueue the packing, the
+// build and the search, check the coordinates, then write the answers.
+// Blocking; `n` laid out in device memory.
+int run_indexed_nn(const char* fn, IndexedNn& n, const float* q_xyz, int64_t nq, const float* ref_xyz, int64_t n_ref,
+                   int32_t* idx, float* d2, hipStream_t s)
+{
+    std::vector<char> blob;
+    int flag = 0;
+    hipLaunchKernelGGL(fill_i32_kernel, grid1d(n.zero_bytes / 4, 256), dim3(256), 0, s, (int*)n.zero, n.zero_bytes / 4,
+                       0);
+    hipLaunchKernelGGL(pack_points_kernel, grid1d(nq, 256), dim3(256), 0, s, q_xyz, nq, nq, n.q4, n.flag);
+    hipLaunchKernelGGL(pack_points_kernel, grid1d(n_ref, 256), dim3(256), 0, s, ref_xyz, n_ref, n_ref, n.r4, n.flag);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = enqueue_index_build(n.plan, blob, n.d_plan, n.b, s);
+    if (e == hipSuccess) {
+        IndexSearchArgs a{};
+        a.desc = (const IndexDesc*)n.d_plan;
+        a.nodes = n.b.nodes;
+        a.queries = n.q4;
+        a.keys = n.keys;
+        a.K = 1;
+        a.m = (int32_t)nq;
+        launch_index_nn(default_index_lanes(nq), n.plan.desc[0].levels, nq, 1, a, s);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(&flag, n.flag, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess && flag) return fail(STEIN_ICP_E_INVALID, "a coordinate is non-finite or above 1e9");
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(nn_finish_kernel, grid1d(nq, 256), dim3(256), 0, s, n.keys, n.q4, n.r4, n_ref, nq, 1, 1, idx,
+                           d2);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(STEIN_ICP_E_DEVICE, std::string(fn) + ": " + hipGetErrorString(e));
+    return STEIN_ICP_OK;
+}
+
+// Whether a stand-alone search of nq queries among n_ref references builds an
+// index first: where the brute-force search costs more than the build. Whole
+// calls, us, index against brute force, either side of the lines: FP32
+// 4,096 x 1,000 84 / 70, x 20,000 87 / 124; 500 x 100,000 129 / 112;
+// 10,000 x 5,000 130 / 105, x 20,000 133 / 154; 100,000 x 1,000 231 / 163,
+// x 5,000 234 / 340. The screens read the cloud back for its centroid first
+// (host_centre): FP16 500 x 100 79 / 83; 30,000 x 100 203 / 172, x 5,000
+// 202 / 220; 100,000 x 100 225 / 353.
+bool nn_builds_index(int64_t nq, int64_t n_ref, bool host_centre)
+{
+    if (n_ref > kIndexMaxRef) return false;
+    const double pairs = (double)nq * (double)n_ref;
+    if (host_centre) return n_ref <= kChunk || n_ref > 65536 || pairs >= 3e7;
+    return n_ref <= kChunk ? n_ref >= 1024 && pairs >= 3e7 : pairs >= 2.5e8;
 }
 
 // The brute-force screens' centres and reference fragments, from the packed
@@ -1195,8 +1332,11 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     if (flag & 2) return bail(fail(STEIN_ICP_E_INVALID, "a schedule index lies outside [0, n_src)"));
     if (flag & 4) return bail(fail(STEIN_ICP_E_INVALID, "an initial particle is non-finite"));
     if (plane) {
-        for (const auto& pd : uref) {
-            rc = run_knn(c->ref4 + pd.ref_off, pd.n_ref, c->ref4 + pd.ref_off, pd.n_ref, cfg->normal_k, nullptr,
+        for (size_t u = 0; u < uref.size(); ++u) {
+            const PairDesc& pd = uref[u];
+            rc = c->indexed ? run_index_normals(plan.desc[u], c->d_idesc + u, c->nodes, c->ref4 + pd.ref_off,
+                                                cfg->normal_k, c->nrm + 4 * pd.ref_off, s)
+                            : run_knn(c->ref4 + pd.ref_off, pd.n_ref, c->ref4 + pd.ref_off, pd.n_ref, cfg->normal_k, nullptr,
                          nullptr, c->nrm + 4 * pd.ref_off, 4, nullptr, s);
             if (rc) return bail(rc);
         }
@@ -1529,6 +1669,17 @@ int stein_icp_nn(const float* q_xyz, int64_t nq, const float* ref_xyz, int64_t n
     if (nq == 0) return STEIN_ICP_OK;
     if (!q_xyz || !ref_xyz || !idx) return fail(STEIN_ICP_E_INVALID, "a pointer is NULL");
     hipStream_t s = (hipStream_t)hip_stream;
+    if (nn_builds_index(nq, n_ref, is_screen(mode))) {
+        IndexedNn n(nq, n_ref);
+        char* mem = nullptr;
+        if (n.fits && hipMalloc(&mem, (size_t)n.bytes) == hipSuccess) {
+            n.layout(mem, nq, n_ref);
+            const int rc = run_indexed_nn("stein_icp_nn", n, q_xyz, nq, ref_xyz, n_ref, idx, d2, s);
+            (void)hipFree(mem);
+            return rc;
+        }
+        (void)hipGetLastError();   // no memory for the index: search without
+    }
     PairDesc pd{};
     pd.q_off = 0;
     pd.nq = nq;
@@ -1765,6 +1916,14 @@ int stein_icp_nn_noalloc(const float* q_xyz, int64_t nq, const float* ref_xyz, i
     char* base = nullptr;
     int rc = scratch_on_device(&base);
     if (rc) return rc;
+    if (nn_builds_index(nq, n_ref, false)) {   // its screens find the centroid on the device
+        IndexedNn n(nq, n_ref);
+        if (n.fits && n.bytes <= (int64_t)kNoAllocScratchBytes) {
+            n.layout(base, nq, n_ref);
+            return run_indexed_nn("stein_icp_nn_noalloc", n, q_xyz, nq, ref_xyz, n_ref, idx, d2,
+                                  (hipStream_t)hip_stream);
+        }
+    }
     int64_t off = 0;
     const auto take = [&](int64_t bytes) {
         char* p = base + off;

@@ -99,3 +99,38 @@ def test_queries_that_are_not_finite_match_the_first_reference():
     got = _matches(src, ref, theta)
     np.testing.assert_array_equal(got[0], oracle.nn_f32(src, ref)[0])
     np.testing.assert_array_equal(got[1], 0)
+
+
+@pytest.mark.parametrize("k", [3, 10, 16, 17, 32])
+def test_normals_from_the_index_equal_the_brute_force_ones(k):
+    """A point-to-plane context takes its neighbourhoods from the index, the
+    stand-alone call by brute force: the same k smallest (distance, index)
+    keys, so the same normals bit for bit."""
+    for n in (5, 16, 257, 4096, 4097, 20011):
+        for kind in ("uniform", "grid"):
+            rng = np.random.default_rng(n + k)
+            ref = dev(_cloud(kind, n, rng))
+            cfg = S.stein_icp_default_config(num_particles=2, batch_size=4, metric=S.METRIC_PLANE, normal_k=k)
+            print(f"normals {kind} n={n} k={k}", flush=True)
+            sol = S.SteinICP(cfg, dev(_cloud("uniform", 8, rng)), ref, dev(np.zeros((2, 6))),
+                             dev(np.arange(4, dtype=np.int32)[None]))
+            got = sol.normals(n)
+            sol.close()
+            want = S.stein_icp_normals(ref, k)
+            np.testing.assert_array_equal(got.cpu().numpy().reshape(-1, 3), want.cpu().numpy().reshape(-1, 3))
+
+
+@pytest.mark.parametrize("mode", [S.NN_FP32, S.NN_BF16_RERANK, S.NN_F16_RERANK])
+def test_stand_alone_search_with_and_without_an_index(mode):
+    """Sizes on either side of the rule that builds an index for one search;
+    queries and references on a whole-number grid (ties)."""
+    for nq, n in ((7, 4097), (3000, 4097), (20000, 700), (40000, 4096), (9000, 12000), (140000, 9000), (2000, 100001)):
+        rng = np.random.default_rng(n)
+        q, ref = _cloud("grid", nq, rng), _cloud("grid" if n % 2 else "uniform", n, rng)
+        q[::3] += rng.uniform(-0.5, 0.5, (len(q[::3]), 3)).astype(np.float32)
+        print(f"nn mode {mode} nq={nq} n={n}", flush=True)
+        idx, d2 = S.stein_icp_nn(dev(q), dev(ref), mode)
+        pick = rng.choice(nq, min(nq, 2000), replace=False)
+        want, want_d = oracle.nn_f32(q[pick], ref)
+        np.testing.assert_array_equal(idx.cpu().numpy()[pick], want)
+        np.testing.assert_array_equal(d2.cpu().numpy()[pick], want_d)
