@@ -58,10 +58,10 @@ extern "C" {
  * by a power of two and split into two FP16 parts (FP16's 11-bit significand
  * carries in two parts what BF16 needs three for): one matrix product per
  * block of references instead of two, with an error bound of the same size.
- * All three modes return the same answers. A context indexes its references
- * at init (clouds up to 2^24 points) and then searches the index, in every
- * mode and with the same answers, unless stein_icp_set_nn_tiling asks for the
- * mode's brute-force search. */
+ * All three modes return the same answers. A context whose searches repay it
+ * indexes its references at init (clouds up to 2^24 points) and then searches
+ * the index, in every mode and with the same answers, unless
+ * stein_icp_set_nn_tiling asks for the mode's brute-force search. */
 enum { STEIN_ICP_NN_FP32 = 0, STEIN_ICP_NN_BF16_RERANK = 1, STEIN_ICP_NN_F16_RERANK = 2 };
 /* Update rule: Adam on -phi (Sec. V), or theta += lr * phi (Eq. 12). */
 enum { STEIN_ICP_OPT_ADAM = 0, STEIN_ICP_OPT_SGD = 1 };

@@ -23,14 +23,16 @@ inline size_t grad_bw_lds_bytes(int K)
 
 // grid: 2 bw_pairs + ceil(P K / kGradGroups) workgroups of kSvgdThreads
 // threads. bw_pairs is P, or 0 when the bandwidths are constants (a fixed
-// bandwidth, or K = 1) written once at init.
+// bandwidth, or K = 1) written once at init. ready: the launch before has
+// left the distances between the particles in the scratch.
 __global__ __launch_bounds__(kSvgdThreads) void grad_bandwidth_kernel(GradArgs g, SvgdArgs v, int32_t n_pairs,
-                                                                      int32_t bw_pairs)
+                                                                      int32_t bw_pairs, int32_t ready)
 {
     extern __shared__ double lds[];
     const int64_t bw_blocks = 2 * (int64_t)bw_pairs;
     if ((int64_t)blockIdx.x < bw_blocks) {   // whole workgroup
-        bandwidth_role<kSvgdThreads>(v, blockIdx.x, bandwidth_keyable(v.K) ? kKeysInLds : kDistancesInGlobal, lds);
+        bandwidth_role<kSvgdThreads>(v, blockIdx.x, bandwidth_keyable(v.K) ? kKeysInLds : kDistancesInGlobal,
+                                     ready != 0, lds);
         return;
     }
     const int64_t wg = (int64_t)blockIdx.x - bw_blocks;

@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "svgd_select.hpp"
 
 namespace sicp {
 
@@ -716,6 +717,12 @@ struct IndexSearchArgs {
     const float4* queries;    // pair p's at p K m: query k m + i
     uint64_t* keys;           // (distance bits, original index), as the queries
     int32_t K, m;
+    // side_blocks > 0: each pair's first side_blocks workgroups work on its
+    // bandwidths instead, beside the search: BW, two of them select the
+    // medians; else they form the distances between the particles, from which
+    // the next launch selects
+    int32_t side_blocks, side_form;
+    SvgdArgs side;
 };
 
 // Key of no match yet: distance infinity, reference 0 (what the brute-force
@@ -725,17 +732,23 @@ constexpr uint64_t kIndexNoMatch = 0x7f80000000000000ull;
 // Threads of a search workgroup: 16 queries. Larger ones hold their slots
 // until the last of more queries ends (4 lanes, street scan: 64 threads 62.6
 // us a launch, 128 65.0, 256 66.6).
-constexpr int search_threads(int lanes) { return 16 * lanes; }
+// With the bandwidths beside the search, the selection's 1,024.
+constexpr int search_threads(int lanes, bool bw = false) { return bw ? kSvgdThreads : 16 * lanes; }
 
 // Dynamic LDS: a thread's remaining distances, per box level.
-template <int L>
+template <int L, bool BW = false>
 inline size_t index_nn_lds_bytes(int levels)
 {
-    return (size_t)(levels - 1) * search_threads(L) * (kFan / L) * 4;
+    return (size_t)(levels - 1) * search_threads(L, BW) * (kFan / L) * 4;
 }
 
-// grid (ceil(K m / 16), pairs), search_threads(L) threads; dynamic LDS
-// index_nn_lds_bytes<L>(most levels of the clouds). A query to L lanes; the
+// Workgroups of `threads` threads for the distances between K particles: a
+// wavefront per particle and kernel.
+inline int pair_distance_blocks(int K, int threads) { return (2 * K * kWave + threads - 1) / threads; }
+
+// grid (side_blocks + ceil(K m L / T), pairs), T = search_threads(L, BW)
+// threads; dynamic LDS index_nn_lds_bytes<L, BW>(most levels of the clouds)
+// and what the bandwidths need. A query to L lanes; the
 // queries are ordered by minibatch point, then particle, so that those of a
 // wavefront look for (nearly) the same place and read the same blocks.
 //
@@ -750,10 +763,10 @@ inline size_t index_nn_lds_bytes(int levels)
 // (slower throughout: the staging and the occupancy cost more than the
 // loads), a second query in turn per group (street 72 -> 82), fan-out 64 on
 // 16 lanes (tabletop 16.6, street 112) and 4 on one lane (41, 94).
-template <int L>
-__global__ __launch_bounds__(search_threads(L)) void index_nn_kernel(IndexSearchArgs a)
+template <int L, bool BW>
+__global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_kernel(IndexSearchArgs a)
 {
-    constexpr int T = search_threads(L);
+    constexpr int T = search_threads(L, BW);
     constexpr int E = kFan / L;                   // entries of a block per lane
     constexpr uint32_t kInf = 0x7f800000u, kEntry = kFan - 1;
     extern __shared__ float4 lds4[];
@@ -761,6 +774,16 @@ __global__ __launch_bounds__(search_threads(L)) void index_nn_kernel(IndexSearch
     __shared__ int32_t level_off[kIndexLevels];
     const int tid = threadIdx.x;
     const int64_t p = blockIdx.y;
+    const int wg = (int)blockIdx.x - a.side_blocks;
+    if (wg < 0) {   // whole workgroup
+        if constexpr (BW) {
+            bandwidth_role<T>(a.side, 2 * p + blockIdx.x, a.side_form, false, (double*)lds4);
+        } else {
+            const int row = uniform(((int)blockIdx.x * T + tid) / kWave);
+            if (row < 2 * a.K) pair_distances_row(a.side.theta, a.side.dscr, a.K, p, row / a.K, row % a.K);
+        }
+        return;
+    }
     const IndexDesc& d = a.desc[a.cloud ? a.cloud[p] : 0];
     const int top = d.levels - 1;
     const float* __restrict__ nodes = (const float*)(a.nodes + d.level_off[0]);
@@ -768,7 +791,7 @@ __global__ __launch_bounds__(search_threads(L)) void index_nn_kernel(IndexSearch
     if (tid < kIndexLevels) level_off[tid] = 4 * (int32_t)(d.level_off[tid] - d.level_off[0]);
     __syncthreads();
     const uint32_t nq = (uint32_t)a.K * (uint32_t)a.m;   // at most 2^31
-    const uint32_t w = blockIdx.x * (T / L) + tid / L;
+    const uint32_t w = (uint32_t)wg * (T / L) + tid / L;
     if (w >= nq) return;   // whole groups; no barrier below
     const uint64_t qi = p * (uint64_t)nq + (uint64_t)(w % (uint32_t)a.K) * (uint32_t)a.m + w / (uint32_t)a.K;
     float4 q = a.queries[qi];

@@ -244,7 +244,14 @@ bool const_bandwidth(const stein_icp_config& c)
 // in the gradient launch: the selection's registers would cost it
 // occupancy.) Every workgroup of the launch takes the dynamic LDS, so the
 // bound keeps two search workgroups per compute unit.
+// Beside the indexed search the selection has 64 registers, so that two
+// workgroups of 1,024 threads share a compute unit, and spills some; up to
+// kBesideSearchK particles it still hides (K = 100: box 26.7 -> 25.5 us an
+// iteration, tabletop 32.3 -> 30.8, against distances beside the search and
+// selection beside the gradients, which is faster for more: K = 300, street
+// 121 -> 111).
 constexpr size_t kFusedBandwidthLds = 48 * 1024;
+constexpr int kBesideSearchK = 128;
 int g_num_cus = 256;   // compute units of the device, read at the first init
 
 // Where the fused bandwidth workgroups keep the pair distances: keys in LDS
@@ -261,7 +268,10 @@ bool fused_bandwidth(const stein_icp_ctx* ctx)
     const stein_icp_config& c = ctx->cfg;
     const int64_t pairs = ctx->P;
     const int K = c.num_particles;
-    return is_screen(c.nn_mode) && !ctx->indexed && !const_bandwidth(c) &&
+    if (ctx->indexed)
+        return !const_bandwidth(c) && K <= kBesideSearchK && ctx->tiling.lanes == 16 &&
+               pairs * K <= 2 * (int64_t)g_num_cus;
+    return is_screen(c.nn_mode) && !const_bandwidth(c) &&
            bandwidth_role_lds_bytes(K, fused_bandwidth_form(K)) <= kFusedBandwidthLds &&
            pairs * K <= 2 * (int64_t)g_num_cus;
 }
@@ -525,12 +535,22 @@ SvgdArgs svgd_args(const stein_icp_ctx* c)
     return v;
 }
 
-// Indexed search: `lanes` lanes per query, nq queries for each pair.
-void launch_index_nn(int lanes, int levels, int64_t nq, int64_t pairs, const IndexSearchArgs& a, hipStream_t s)
+// Indexed search: `lanes` lanes per query, nq queries for each pair; bw: the
+// bandwidths beside it (16 lanes).
+void launch_index_nn(int lanes, bool bw, int levels, int64_t nq, int64_t pairs, const IndexSearchArgs& a,
+                     hipStream_t s)
 {
-    const dim3 grid((unsigned)ceil_div(nq, 16), (unsigned)pairs), block(search_threads(lanes));
-    if (lanes == 4) hipLaunchKernelGGL(index_nn_kernel<4>, grid, block, index_nn_lds_bytes<4>(levels), s, a);
-    else hipLaunchKernelGGL(index_nn_kernel<16>, grid, block, index_nn_lds_bytes<16>(levels), s, a);
+    const int T = search_threads(lanes, bw);
+    const dim3 grid((unsigned)(a.side_blocks + ceil_div(nq * lanes, T)), (unsigned)pairs), block(T);
+    if (bw) {
+        const size_t lds = std::max(index_nn_lds_bytes<16, true>(levels),
+                                    bandwidth_role_lds_bytes(a.side.K, a.side_form));
+        hipLaunchKernelGGL((index_nn_kernel<16, true>), grid, block, lds, s, a);
+    } else if (lanes == 4) {
+        hipLaunchKernelGGL((index_nn_kernel<4, false>), grid, block, index_nn_lds_bytes<4>(levels), s, a);
+    } else {
+        hipLaunchKernelGGL((index_nn_kernel<16, false>), grid, block, index_nn_lds_bytes<16>(levels), s, a);
+    }
 }
 
 // Queries of the coming iteration from the current poses and step count.
@@ -555,7 +575,13 @@ hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
             a.keys = c->partial;
             a.K = c->K;
             a.m = c->m;
-            launch_index_nn(c->tiling.lanes, c->index_levels, c->nq, c->P, a, s);
+            const bool bw = fused_bandwidth(c);
+            if (!const_bandwidth(c->cfg)) {
+                a.side = svgd_args(c);
+                a.side_form = fused_bandwidth_form(c->K);
+                a.side_blocks = bw ? 2 : pair_distance_blocks(c->K, search_threads(c->tiling.lanes));
+            }
+            launch_index_nn(c->tiling.lanes, bw, c->index_levels, c->nq, c->P, a, s);
             return hipGetLastError();
         }
         if (is_screen(c->cfg.nn_mode)) {
@@ -597,7 +623,7 @@ hipError_t enqueue_stage(const stein_icp_ctx* c, int stage, hipStream_t s)
     const int32_t bw_pairs = const_bandwidth(c->cfg) || fused_bandwidth(c) ? 0 : c->P;
     const int64_t blocks = 2 * (int64_t)bw_pairs + ceil_div((int64_t)c->P * c->K, kGradGroups);
     hipLaunchKernelGGL(grad_bandwidth_kernel, dim3((unsigned)blocks), dim3(kSvgdThreads), grad_bw_lds_bytes(c->K), s,
-                       g, svgd_args(c), c->P, bw_pairs);
+                       g, svgd_args(c), c->P, bw_pairs, c->indexed ? 1 : 0);
     return hipGetLastError();
     }
     const SvgdArgs v = svgd_args(c);
@@ -916,6 +942,22 @@ void free_ctx(stein_icp_ctx* c)
     delete c;
 }
 
+// Whether a context's searches repay an index. Below 1.5e7 pair evaluations an
+// iteration the FP32 brute-force search is as fast or faster (us an
+// iteration, brute force / index: 512 queries x 4,000 19.4 / 23.7, x 20,000
+// 24.9 / 28.0; 10,000 x 1,000 25.4 / 25.6; 5,000 x 4,000 30.0 / 25.1); the
+// screens are only with few queries (512 x 4,000 22.2 / 23.7; 1,600 x 300
+// 25.9 / 22.3).
+bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
+{
+    double evals = 0.0, queries = 0.0;
+    for (const auto& pd : pairs) {
+        evals += (double)pd.nq * (double)pd.n_ref;
+        queries += (double)pd.nq;
+    }
+    return evals >= 1.5e7 || (is_screen(c.nn_mode) && queries > 1024.0);
+}
+
 // Device memory of an index build besides the nodes and the plan.
 struct IndexScratch {
     size_t plan = 0, split = 0, state = 0, hist = 0;   // bytes
@@ -1031,7 +1073,7 @@ int run_indexed_nn(const char* fn, IndexedNn& n, const float* q_xyz, int64_t nq,
         a.keys = n.keys;
         a.K = 1;
         a.m = (int32_t)nq;
-        launch_index_nn(default_index_lanes(nq), n.plan.desc[0].levels, nq, 1, a, s);
+        launch_index_nn(default_index_lanes(nq), false, n.plan.desc[0].levels, nq, 1, a, s);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(&flag, n.flag, sizeof(int), hipMemcpyDeviceToHost, s);
@@ -1192,7 +1234,7 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     {
         std::vector<std::pair<int64_t, int64_t>> clouds;
         for (const auto& pd : uref) clouds.push_back({pd.ref_off, pd.n_ref});
-        c->indexed = index_plan(clouds, plan);
+        c->indexed = index_pays(*cfg, c->pairs) && index_plan(clouds, plan);
         if (!c->indexed) plan = IndexPlan();
         for (const auto& d : plan.desc) c->index_levels = std::max(c->index_levels, (int)d.levels);
     }

@@ -592,16 +592,38 @@ __host__ __device__ inline bool bandwidth_keyable(int K) { return (int64_t)K * (
 // memory. All three find the same exact order statistics.
 enum BandwidthForm : int32_t { kKeysInLds = 0, kKeysInGlobal = 1, kDistancesInGlobal = 2 };
 
+// The distances of particle k to those after it, by one wavefront, into the
+// scratch: 16-bit keys where the selection takes them, else FP64. One
+// workgroup forming all of them in turn took most of the bandwidths' time
+// (45,000 pairs: about 20 of 32 us); spread over the launch before, they cost
+// it nothing measurable.
+__device__ __forceinline__ void pair_distances_row(const double* __restrict__ theta, double* __restrict__ dscr, int K,
+                                                   int64_t p, int rot, int k)
+{
+    const double* th = theta + p * K * 6;
+    double* out = dscr + (p * 2 + rot) * ((int64_t)K * (K - 1) / 2);
+    const int64_t row = tri_row(k, K);
+    double tk[6];
+    for (int d = 0; d < 6; ++d) tk[d] = th[6 * k + d];
+    const bool keyed = bandwidth_keyable(K);
+    for (int l = k + 1 + (int)(threadIdx.x & (kWave - 1)); l < K; l += kWave) {
+        const double x = rot ? dist2_rot(tk, th + 6 * l) : dist2_trans(tk, th + 6 * l);
+        if (keyed) reinterpret_cast<uint16_t*>(out)[row + (l - k - 1)] = order_key(x);
+        else out[row + (l - k - 1)] = x;
+    }
+}
+
 // grid (pairs, 2), 1024 threads. blockIdx.y: 0 translation, 1 rotation.
 // Dynamic LDS: K x 6 particles (FP64) followed by the 16-bit pair keys.
 // Median-heuristic bandwidth of pair p, block rot (0 translation, 1
 // rotation), by one NT-thread workgroup; `sh` and `dyn`
 // (bandwidth_lds_bytes(K, form)) are the workgroup's LDS. `form`
 // (BandwidthForm; the key forms only where bandwidth_keyable(K)) places the
-// pair distances.
+// pair distances. `ready`: an earlier launch has left them in the scratch
+// (pair_distances_row).
 template <int NT>
-__device__ __forceinline__ void bandwidth_body(const SvgdArgs& a, int64_t p, int rot, int form, SelectShared& sh,
-                                               double* dyn)
+__device__ __forceinline__ void bandwidth_body(const SvgdArgs& a, int64_t p, int rot, int form, bool ready,
+                                               SelectShared& sh, double* dyn)
 {
     const int K = a.K;
     const int tid = threadIdx.x;
@@ -621,7 +643,27 @@ __device__ __forceinline__ void bandwidth_body(const SvgdArgs& a, int64_t p, int
         // the keys, their range (per wavefront) and the cleared histogram
         // of the selection, under one barrier
         uint32_t kmin = 0xffffu, kmax = 0u;
-        for (int k = tid >> 6; k < K; k += NT / kWave) {
+        if (ready) {   // copied four at a time (the scratch of a pair and the keys are 8-byte aligned)
+            const uint16_t* from = reinterpret_cast<const uint16_t*>(a.dscr + (p * 2 + rot) * np);
+            auto see = [&](uint32_t x) {
+                kmin = min(kmin, x);
+                kmax = max(kmax, x);
+            };
+            for (int64_t q = tid; q < np / 4; q += NT) {
+                const uint2 v = reinterpret_cast<const uint2*>(from)[q];
+                reinterpret_cast<uint2*>(key)[q] = v;
+                see(v.x & 0xffffu);
+                see(v.x >> 16);
+                see(v.y & 0xffffu);
+                see(v.y >> 16);
+            }
+            const int64_t q = np / 4 * 4 + tid;
+            if (q < np) {
+                key[q] = from[q];
+                see(from[q]);
+            }
+        }
+        for (int k = ready ? K : tid >> 6; k < K; k += NT / kWave) {
             const int64_t row = tri_row(k, K);
             for (int l = k + 1 + (tid & (kWave - 1)); l < K; l += kWave) {
                 const uint16_t x = order_key(rot ? dist2_rot(th + 6 * k, th + 6 * l) : dist2_trans(th + 6 * k, th + 6 * l));
@@ -636,7 +678,7 @@ __device__ __forceinline__ void bandwidth_body(const SvgdArgs& a, int64_t p, int
         select_pair_keyed<NT>(key, np, ra, rb, K, rot, th, sh, va, vb);
     } else {
         double* d = a.dscr + (p * 2 + rot) * np;
-        for (int k = tid >> 6; k < K; k += NT / kWave) {
+        for (int k = ready ? K : tid >> 6; k < K; k += NT / kWave) {
             const int64_t row = tri_row(k, K);
             for (int l = k + 1 + (tid & (kWave - 1)); l < K; l += kWave)
                 d[row + (l - k - 1)] = rot ? dist2_rot(th + 6 * k, th + 6 * l) : dist2_trans(th + 6 * k, th + 6 * l);
@@ -672,11 +714,11 @@ inline size_t bandwidth_role_lds_bytes(int K, int form)
 // Bandwidth workgroup b of a launch (pair b / 2, block b % 2) on NT threads;
 // lds: its dynamic LDS of bandwidth_role_lds_bytes(K, form) bytes.
 template <int NT>
-__device__ __forceinline__ void bandwidth_role(const SvgdArgs& v, int64_t b, int form, double* lds)
+__device__ __forceinline__ void bandwidth_role(const SvgdArgs& v, int64_t b, int form, bool ready, double* lds)
 {
     SelectShared& sh = *reinterpret_cast<SelectShared*>(lds);
     double* dyn = lds + (sizeof(SelectShared) + 15) / 16 * 2;
-    bandwidth_body<NT>(v, b >> 1, (int)(b & 1), form, sh, dyn);
+    bandwidth_body<NT>(v, b >> 1, (int)(b & 1), form, ready, sh, dyn);
 }
 
 }  // namespace sicp

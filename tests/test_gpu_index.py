@@ -41,12 +41,18 @@ def _cloud(kind, n, rng):
 
 
 def _matches(src, ref, theta, **cfg):
-    K, m = len(theta), len(src)
+    """Matches of the given particles, in a context of so many (repeated) that
+    a screen's searches repay an index."""
+    n, m = len(theta), len(src)
+    K = max(n, 1100 // m + 1)
+    theta = theta[np.arange(K) % n]
     c = S.stein_icp_default_config(num_particles=K, batch_size=m, **cfg)
     sol = S.SteinICP(c, dev(src), dev(ref), dev(theta), dev(np.arange(m, dtype=np.int32)[None]))
     try:
         sol.step(1)
-        return sol.diagnostics()["match"].cpu().numpy().reshape(K, m)
+        got = sol.diagnostics()["match"].cpu().numpy().reshape(K, m)
+        np.testing.assert_array_equal(got, got[np.arange(K) % n])
+        return got[:n]
     finally:
         sol.close()
 
@@ -60,7 +66,7 @@ def test_index_matches_equal_the_brute_force_search(kind):
         # identity, a move inside the cloud and one far outside, all exact in FP32
         theta = np.array([[0, 0, 0, 0, 0, 0], [1, -2, 3, 0, 0, 0], [4096, 0, -512, 0, 0, 0]], np.float64)
         print(f"{kind} n={n}", flush=True)
-        got = _matches(src, ref, theta, nn_mode=S.NN_F16_RERANK if n % 2 else S.NN_FP32)
+        got = _matches(src, ref, theta, nn_mode=S.NN_F16_RERANK if n % 2 else S.NN_BF16_RERANK)
         for k in range(3):
             q = (src.astype(np.float64) + theta[k, :3]).astype(np.float32)
             np.testing.assert_array_equal(got[k], oracle.nn_f32(q, ref)[0], err_msg=f"{kind} n={n} k={k}")
@@ -96,7 +102,7 @@ def test_queries_that_are_not_finite_match_the_first_reference():
     ref, src = _cloud("uniform", 5000, rng), _cloud("uniform", 32, rng)
     theta = np.zeros((2, 6))
     theta[1, 0] = 1e300
-    got = _matches(src, ref, theta)
+    got = _matches(src, ref, theta, nn_mode=S.NN_F16_RERANK)
     np.testing.assert_array_equal(got[0], oracle.nn_f32(src, ref)[0])
     np.testing.assert_array_equal(got[1], 0)
 
@@ -110,9 +116,10 @@ def test_normals_from_the_index_equal_the_brute_force_ones(k):
         for kind in ("uniform", "grid"):
             rng = np.random.default_rng(n + k)
             ref = dev(_cloud(kind, n, rng))
-            cfg = S.stein_icp_default_config(num_particles=2, batch_size=4, metric=S.METRIC_PLANE, normal_k=k)
+            cfg = S.stein_icp_default_config(num_particles=300, batch_size=4, metric=S.METRIC_PLANE, normal_k=k,
+                                             nn_mode=S.NN_F16_RERANK)
             print(f"normals {kind} n={n} k={k}", flush=True)
-            sol = S.SteinICP(cfg, dev(_cloud("uniform", 8, rng)), ref, dev(np.zeros((2, 6))),
+            sol = S.SteinICP(cfg, dev(_cloud("uniform", 8, rng)), ref, dev(np.zeros((300, 6))),
                              dev(np.arange(4, dtype=np.int32)[None]))
             got = sol.normals(n)
             sol.close()
@@ -134,3 +141,26 @@ def test_stand_alone_search_with_and_without_an_index(mode):
         want, want_d = oracle.nn_f32(q[pick], ref)
         np.testing.assert_array_equal(idx.cpu().numpy()[pick], want)
         np.testing.assert_array_equal(d2.cpu().numpy()[pick], want_d)
+
+
+@pytest.mark.parametrize("K", [2, 100, 128, 129, 300, 346, 347])
+def test_bandwidths_of_an_indexed_context(K):
+    """The medians selected beside the search (up to 128 particles), from the
+    distances formed beside it (more; 16-bit keys up to 346, FP64 beyond), and
+    by the brute-force context's launch are the same bits."""
+    rng = np.random.default_rng(K)
+    m = 1100 // K + 1
+    src, ref = dev(_cloud("uniform", m + 5, rng)), dev(_cloud("uniform", 3000, rng))
+    theta, sched = dev(rng.uniform(-0.4, 0.4, (K, 6))), dev(np.arange(m, dtype=np.int32)[None])
+    out = []
+    for tiling in (None, (1, 4, 1024)):
+        sol = S.SteinICP(S.stein_icp_default_config(num_particles=K, batch_size=m, nn_mode=S.NN_F16_RERANK), src, ref,
+                         theta, sched)
+        if tiling:
+            sol.set_tiling(*tiling)
+        sol.step(3)
+        out.append((sol.diagnostics()["h"].cpu().numpy(), sol.particles().cpu().numpy()))
+        sol.close()
+    print(f"K={K} h={out[0][0]}", flush=True)
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
