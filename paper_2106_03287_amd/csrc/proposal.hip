@@ -156,6 +156,7 @@ struct stein_icp_proposal {
     unsigned long long* pool_keys;
     float *G0, *G1, *G2, *dA3, *dA2, *dA1;   // winner rows of the sparse backward (F3 per cloud)
     float *ws, *colpart, *prep;
+    double* mmd_part;   // the shares of the set loss
     int64_t ws_floats, colpart_floats;
     int64_t step = 0;
     int32_t last_batch = 0;   // batch of the last loss call (0: no gradient yet)
@@ -280,15 +281,16 @@ int backward(Model* m, hipStream_t s, const float* X, int64_t B)
     return STEIN_ICP_OK;
 }
 
+// `parts` workgroups a sample; part: B x parts doubles (loss itself for one).
 int launch_mmd(hipStream_t s, const float* Xf, const double* Xd, const double* Y, int64_t B, int32_t K,
-               const MmdScales& sc, double gscale, float* dX, double* loss)
+               const MmdScales& sc, double gscale, float* dX, int32_t parts, double* part, double* loss)
 {
-    // X and Y sets plus the gradient partials of max(1, 256 / K) row groups
-    // (K <= 1024 keeps it within 144 KiB)
-    const size_t lds = sizeof(double) * (12 * (size_t)K + 6 * (size_t)std::max(1, 256 / K) * K);
+    // X and Y sets plus the gradient partials (K <= 1024 keeps it within 108 KiB)
+    const size_t lds = sizeof(double) * (12 * (size_t)K + 6 * 256);
     if (lds > 65536)
         HIP_TRY(hipFuncSetAttribute((const void*)mmd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    mmd_kernel<<<(unsigned)B, 256, lds, s>>>(Xf, Xd, Y, K, sc, gscale, dX, loss);
+    mmd_kernel<<<dim3((unsigned)B, (unsigned)parts), 256, lds, s>>>(Xf, Xd, Y, K, sc, gscale, dX, part);
+    mmd_loss_kernel<<<(unsigned)ceil_div(B, 256), 256, 0, s>>>(part, B, parts, K, loss);
     HIP_TRY(hipGetLastError());
     return STEIN_ICP_OK;
 }
@@ -370,7 +372,7 @@ int stein_icp_proposal_create(stein_icp_proposal** out, const stein_icp_proposal
     const size_t o_dY = take(4 * m->Bmax * K6), o_dZ = take(4 * m->Bmax * kFz), o_dF = take(4 * m->Bmax * kFcat);
     const size_t o_flags = take(4 * m->Bmax);
     const size_t o_ws = take(4 * m->ws_floats), o_cp = take(4 * m->colpart_floats);
-    const size_t o_prep = take(4 * 2 * 3 * m->P);
+    const size_t o_prep = take(4 * 2 * 3 * m->P), o_mmd = take(8 * kMmdParts * (size_t)m->Bmax);
     if (hipMalloc(&m->arena, off) != hipSuccess) {
         (void)hipGetLastError();
         m->arena = nullptr;
@@ -405,6 +407,7 @@ int stein_icp_proposal_create(stein_icp_proposal** out, const stein_icp_proposal
     m->ws = (float*)(a + o_ws);
     m->colpart = (float*)(a + o_cp);
     m->prep = (float*)(a + o_prep);
+    m->mmd_part = (double*)(a + o_mmd);
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&m->num_cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -578,7 +581,8 @@ int stein_icp_proposal_loss(stein_icp_proposal* m, const float* clouds, const do
     if (B < 1 || B > m->Bmax) return fail(STEIN_ICP_E_INVALID, "batch must be in [1, max_batch]");
     hipStream_t s = (hipStream_t)stream;
     CHECK(forward(m, s, clouds, B));
-    CHECK(launch_mmd(s, m->Y, nullptr, targets, B, (int32_t)m->K, m->scales, 1.0 / B, m->dY, loss));
+    CHECK(launch_mmd(s, m->Y, nullptr, targets, B, (int32_t)m->K, m->scales, 1.0 / B, m->dY, kMmdParts, m->mmd_part,
+                     loss));
     CHECK(backward(m, s, clouds, B));
     if (grad) HIP_TRY(hipMemcpyAsync(grad, m->grad, 4 * m->n_params, hipMemcpyDeviceToDevice, s));
     m->last_batch = B;
@@ -607,7 +611,7 @@ int stein_icp_proposal_mmd(const double* X, const double* Y, int32_t B, int32_t 
         return fail(STEIN_ICP_E_INVALID, "need batch >= 1 and K in [1, 1024]");
     MmdScales sc;
     CHECK(make_scales(ns, sigma, sc));
-    return launch_mmd((hipStream_t)stream, nullptr, X, Y, B, K, sc, 0.0, nullptr, out);
+    return launch_mmd((hipStream_t)stream, nullptr, X, Y, B, K, sc, 0.0, nullptr, 1, out, out);
 }
 
 int stein_icp_propose(stein_icp_proposal* m, const float* src, int64_t n_src, const float* ref, int64_t n_ref,

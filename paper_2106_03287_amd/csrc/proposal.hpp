@@ -75,14 +75,50 @@ __device__ __forceinline__ bool gemm_tile(int64_t b, int64_t Mt, int64_t Nt, int
     return mt < Mt;
 }
 
+// Eight consecutive k of one row (or column) of an operand tile, zero outside
+// the matrix. kc: k is the contiguous dimension of global memory (two 16-byte
+// loads where `vec`, the whole operand's rows are aligned to 16 bytes), else
+// rows are (a load takes the same k of 64 consecutive rows).
+__device__ __forceinline__ void gemm_load(const float* __restrict__ A, bool kc, bool vec, int64_t ld, int64_t row,
+                                          bool in, int64_t k, int64_t kend, float (&v)[8])
+{
+    if (in && k + 8 <= kend) {
+        if (kc && vec) {
+            const float4 x = *reinterpret_cast<const float4*>(A + row * ld + k);
+            const float4 y = *reinterpret_cast<const float4*>(A + row * ld + k + 4);
+            v[0] = x.x;
+            v[1] = x.y;
+            v[2] = x.z;
+            v[3] = x.w;
+            v[4] = y.x;
+            v[5] = y.y;
+            v[6] = y.z;
+            v[7] = y.w;
+        } else {
+            const float* a = A + (kc ? row * ld + k : k * ld + row);
+            const int64_t st = kc ? 1 : ld;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = a[u * st];
+        }
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = in && k + u < kend ? A[kc ? row * ld + k + u : (k + u) * ld + row] : 0.f;
+}
+
 // 256 threads, 64 x 64 output tile; wavefront w owns the 32 x 32 quarter
 // (w / 2, w % 2) as 2 x 2 MFMA tiles. Both LDS tiles are K-contiguous
 // ([row][k] and [col][k]), so a lane reads the eight K values of its
-// fragment (row lane % 16, K slice 8 (lane / 16)) in one 16-byte load.
+// fragment (row lane % 16, K slice 8 (lane / 16)) in one 16-byte load, and a
+// thread stages the eight K values of one row of each operand in one 16-byte
+// store. The next step's values are loaded while this one is multiplied, into
+// the other of two LDS tiles. Bound by load latency and launch at this model's
+// sizes: the thirteen products of a training step at batch 32 average 9.4 us
+// (36 with a 2-byte store per element and the loads between two barriers).
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t As[kGT][kGK + kLdsPad];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[kGT][kGK + kLdsPad];
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][kGT][kGK + kLdsPad];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kGT][kGK + kLdsPad];
     int64_t mt, nt;
     if (!gemm_tile(blockIdx.x, (g.M + kGT - 1) / kGT, (g.N + kGT - 1) / kGT, mt, nt)) return;   // whole workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,44 +132,45 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
-    for (int64_t k0 = kbeg; k0 < kend; k0 += kGK) {
-        // 8 elements of each operand tile per thread; the thread-to-element
-        // map walks the contiguous dimension of global memory
+    // this thread's row of each operand tile and its eight k of a step: the
+    // threads of a wavefront run along the contiguous dimension
+    const bool akc = !g.ta, bkc = g.tb != 0;
+    const int ar = akc ? tid / 4 : tid % 64, ak = 8 * (akc ? tid % 4 : tid / 64);
+    const int br = bkc ? tid / 4 : tid % 64, bk = 8 * (bkc ? tid % 4 : tid / 64);
+    const bool av = ((uintptr_t)g.A & 15) == 0 && g.lda % 4 == 0, bv = ((uintptr_t)g.B & 15) == 0 && g.ldb % 4 == 0;
+    const bool ain = m0 + ar < g.M, bin = n0 + br < g.N;
+    float va[8], vb[8];
+    auto load = [&](int64_t k0) {
+        gemm_load(g.A, akc, av, g.lda, m0 + ar, ain, k0 + ak, kend, va);
+        gemm_load(g.B, bkc, bv, g.ldb, n0 + br, bin, k0 + bk, kend, vb);
+    };
+    if (kbeg < kend) load(kbeg);
+    int cur = 0;
+    for (int64_t k0 = kbeg; k0 < kend; k0 += kGK, cur ^= 1) {
+        u16x8_t ha, hb;
 #pragma unroll
-        for (int u = 0; u < (kGT * kGK) / 256; ++u) {
-            const int e = tid + 256 * u;
-            const int r = g.ta ? (e % kGT) : (e / kGK);
-            const int k = g.ta ? (e / kGT) : (e % kGK);
-            const int64_t gm = m0 + r, gk = k0 + k;
-            float v = 0.f;
-            if (gm < g.M && gk < kend) v = g.ta ? g.A[gk * g.lda + gm] : g.A[gm * g.lda + gk];
-            As[r][k] = to_bf16(v);
+        for (int u = 0; u < 8; ++u) {
+            ha[u] = to_bf16(va[u]);
+            hb[u] = to_bf16(vb[u]);
         }
-#pragma unroll
-        for (int u = 0; u < (kGT * kGK) / 256; ++u) {
-            const int e = tid + 256 * u;
-            const int c = g.tb ? (e / kGK) : (e % kGT);
-            const int k = g.tb ? (e % kGK) : (e / kGT);
-            const int64_t gn = n0 + c, gk = k0 + k;
-            float v = 0.f;
-            if (gn < g.N && gk < kend) v = g.tb ? g.B[gn * g.ldb + gk] : g.B[gk * g.ldb + gn];
-            Bs[c][k] = to_bf16(v);
-        }
+        *reinterpret_cast<u16x8_t*>(&As[cur][ar][ak]) = ha;
+        *reinterpret_cast<u16x8_t*>(&Bs[cur][br][bk]) = hb;
+        if (k0 + kGK < kend) load(k0 + kGK);
         __syncthreads();
         const int fr = lane & 15, fk = 8 * (lane >> 4);
         bf16x8_t af[2], bfr[2];
 #pragma unroll
         for (int a = 0; a < 2; ++a)
-            af[a] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(&As[wm + 16 * a + fr][fk]));
+            af[a] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(&As[cur][wm + 16 * a + fr][fk]));
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-            bfr[b] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(&Bs[wn + 16 * b + fr][fk]));
+            bfr[b] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(&Bs[cur][wn + 16 * b + fr][fk]));
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
                 acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-        __syncthreads();
+        // the other tile is written next: its readers have passed this step's barrier
     }
     // lane holds column lane % 16 and rows 4 (lane / 16) .. +3 of each tile
     if (g.pool_keys) {
@@ -419,6 +456,7 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ W, int32_t S, int
     if (i >= M * N) return;
     const int64_t m = i / N, n = i % N;
     float s = 0.f;
+#pragma unroll 16   // loads in flight; the sum keeps its order
     for (int32_t z = 0; z < S; ++z) s += W[(int64_t)z * M * N + i];
     if (bias) s += bias[n];
     if (relu) s = fmaxf(s, 0.f);
@@ -565,6 +603,7 @@ __global__ void colsum_partial_kernel(const float* __restrict__ X, int64_t rows,
     if (n >= N) return;
     const int64_t r0 = (int64_t)blockIdx.y * chunk, r1 = min(rows, r0 + chunk);
     float s = 0.f;
+#pragma unroll 16   // loads in flight; the sum keeps its order
     for (int64_t r = r0; r < r1; ++r) s += X[r * N + n];
     part[(int64_t)blockIdx.y * N + n] = s;
 }
@@ -574,6 +613,7 @@ __global__ void colsum_merge_kernel(const float* __restrict__ part, int64_t nch,
     const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= N) return;
     float s = 0.f;
+#pragma unroll 32   // loads in flight; the sum keeps its order
     for (int64_t c = 0; c < nch; ++c) s += part[c * N + n];
     out[n] = s;
 }
@@ -616,21 +656,26 @@ __device__ __forceinline__ double mmd_k(const MmdScales& sc, const double* u, co
     return k;
 }
 
-// One workgroup per sample b: X[b] (K x 6, FP32 network output, or FP64 when
-// Xd is given) against the target set Y[b] (FP64):
+// X[b] (K x 6, FP32 network output, or FP64 when Xd is given) against the
+// target set Y[b] (FP64):
 //   loss[b] = (1 / K^2) sum_ij [k(x_i, x_j) + k(y_i, y_j) - 2 k(x_i, y_j)]
 // (the biased MMD^2 estimate) and, when dX != nullptr,
 //   dX[b] = gscale * d loss[b] / d X[b]
 //         = gscale (2 / K^2) sum_j [grad_u k(x_i, x_j) - grad_u k(x_i, y_j)].
-// Thread t takes row i = t mod K and the j range of group t / K (G groups,
-// G K <= 256); row sums of the groups are added in group order.
+// Workgroup (b, r) takes the rows i of part r of gridDim.y, 256 at a time (G =
+// max(1, 256 / rows) threads to a row, each with a range of j; their sums are
+// added in order), and writes its share of the loss to
+// part[b gridDim.y + r]; mmd_loss_kernel adds the shares. Bound by the FP64
+// exponentials: 32 samples of 100 particles took 115 us with one workgroup a
+// sample, which leaves most of the chip idle, 20 with kMmdParts.
+constexpr int kMmdParts = 16;
 __global__ __launch_bounds__(256) void mmd_kernel(const float* __restrict__ Xf, const double* __restrict__ Xd,
                                                   const double* __restrict__ Y, int32_t K, MmdScales sc,
-                                                  double gscale, float* __restrict__ dX, double* __restrict__ loss)
+                                                  double gscale, float* __restrict__ dX, double* __restrict__ part)
 {
-    extern __shared__ double sm[];   // X, Y (K x 6 each), then G x K x 6 gradient partials
+    extern __shared__ double sm[];   // X, Y (K x 6 each), then 256 x 6 gradient partials
     const int64_t b = blockIdx.x;
-    const int G = max(1, 256 / K);
+    const int i0 = (int)((int64_t)K * blockIdx.y / gridDim.y), i1 = (int)((int64_t)K * (blockIdx.y + 1) / gridDim.y);
     double* x = sm;
     double* y = sm + 6 * K;
     double* gp = sm + 12 * K;
@@ -640,15 +685,14 @@ __global__ __launch_bounds__(256) void mmd_kernel(const float* __restrict__ Xf, 
     }
     __syncthreads();
     __shared__ double red[256];
-    double part = 0.0;
-    // rows beyond 256 / K groups are taken in further passes
-    for (int base = 0; base < K; base += 256) {
-        const int t = threadIdx.x;
-        const int i = base + (K >= 256 ? t : t % K);
-        const int grp = K >= 256 ? 0 : t / K;
-        const bool live = (K >= 256 ? i < K : t < G * K);
-        double g[6] = {0, 0, 0, 0, 0, 0}, du[6];
-        if (live) {
+    double sum = 0.0;
+    const int t = threadIdx.x;
+    const double w = gscale * 2.0 / ((double)K * K);
+    for (int r0 = i0; r0 < i1; r0 += 256) {
+        const int rows = min(256, i1 - r0), G = 256 / rows;
+        if (t < G * rows) {
+            const int row = t % rows, grp = t / rows, i = r0 + row;
+            double g[6] = {0, 0, 0, 0, 0, 0}, du[6];
             const int j0 = (int)((int64_t)K * grp / G), j1 = (int)((int64_t)K * (grp + 1) / G);
             for (int j = j0; j < j1; ++j) {
                 const double kxx = mmd_k(sc, x + 6 * i, x + 6 * j, du);
@@ -657,29 +701,38 @@ __global__ __launch_bounds__(256) void mmd_kernel(const float* __restrict__ Xf, 
                 const double kxy = mmd_k(sc, x + 6 * i, y + 6 * j, du);
 #pragma unroll
                 for (int c = 0; c < 6; ++c) g[c] -= du[c];
-                part += kxx + mmd_k(sc, y + 6 * i, y + 6 * j, nullptr) - 2.0 * kxy;
+                sum += kxx + mmd_k(sc, y + 6 * i, y + 6 * j, nullptr) - 2.0 * kxy;
             }
-            if (dX)
 #pragma unroll
-                for (int c = 0; c < 6; ++c) gp[((int64_t)grp * K + i) * 6 + c] = g[c];
+            for (int c = 0; c < 6; ++c) gp[t * 6 + c] = g[c];
         }
-        if (K < 256) break;   // one pass covers every row when G K >= K
-    }
-    red[threadIdx.x] = part;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+        if (dX)
+            for (int e = t; e < 6 * rows; e += blockDim.x) {
+                double s = 0.0;
+                for (int q = 0; q < G; ++q) s += gp[q * 6 * rows + e];
+                dX[(b * K + r0) * 6 + e] = (float)(w * s);
+            }
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss[b] = red[0] / ((double)K * K);
-    if (!dX) return;
-    const double w = gscale * 2.0 / ((double)K * K);
-    const int Gs = K >= 256 ? 1 : G;
-    for (int e = threadIdx.x; e < 6 * K; e += blockDim.x) {
-        double sum = 0.0;
-        for (int q = 0; q < Gs; ++q) sum += gp[(int64_t)q * 6 * K + e];
-        dX[b * 6 * K + e] = (float)(w * sum);
+    red[t] = sum;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (t < s) red[t] += red[t + s];
+        __syncthreads();
     }
+    if (t == 0) part[b * gridDim.y + blockIdx.y] = red[0];
+}
+
+// loss[b] = (sum of its shares, in order) / K^2.
+__global__ void mmd_loss_kernel(const double* __restrict__ part, int64_t B, int32_t parts, int32_t K,
+                                double* __restrict__ loss)
+{
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B) return;
+    double s = 0.0;
+    for (int r = 0; r < parts; ++r) s += part[b * parts + r];
+    loss[b] = s / ((double)K * K);
 }
 
 // ------------------------------------------------------------- optimiser
