@@ -81,4 +81,28 @@ __device__ __forceinline__ void transform_f64(const double* __restrict__ R, cons
     for (int r = 0; r < 3; ++r) q[r] = ((R[3 * r] * s0 + R[3 * r + 1] * s1) + R[3 * r + 2] * s2) + u[r];
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sum over a wavefront, in all its lanes, in the order of exchanges at
+// distances 32, 16, 8, 4, 2, 1 (all lanes active). Within rows of 16 lanes
+// the exchanges are register moves; at distance 4 a row rotation reaches the
+// partner or its copy 8 lanes on, which holds the same value by then.
+__device__ __forceinline__ double wave_sum(double x)
+{
+    x += __shfl_xor(x, 32);
+    x += __shfl_xor(x, 16);
+    x += dpp_f64<0x128>(x);   // row rotation by 8
+    x += dpp_f64<0x124>(x);   // row rotation by 4
+    x += dpp_f64<0x4e>(x);    // quads 2,3,0,1
+    x += dpp_f64<0xb1>(x);    // quads 1,0,3,2
+    return x;
+}
+
 }  // namespace sicp

@@ -96,15 +96,10 @@ __device__ __forceinline__ void grad_group(const GradArgs& a, int64_t pk, int64_
             }
         }
     }
-    // fixed-shape reduction: a shuffle tree inside each wavefront, then the
+    // fixed-shape reduction: a tree inside each wavefront, then the
     // group's wavefronts in order (one barrier)
 #pragma unroll
-    for (int d = 0; d < 6; ++d) {
-        double x = acc[d];
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        acc[d] = x;
-    }
+    for (int d = 0; d < 6; ++d) acc[d] = wave_sum(acc[d]);
     constexpr int WV = kGradThreads / kWave;   // wavefronts per group
     double* r0 = red + grp * WV * 6;
     const int wv = lt / kWave, lane = lt % kWave;

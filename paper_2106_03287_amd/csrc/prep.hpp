@@ -12,13 +12,10 @@ namespace sicp {
 //   dR/droll = [0 | R2 | -R1]                              (columns)
 //   dR/dpitch= [B0 | B2 sr | B2 cr], B = Rz dRy/dpitch     (columns)
 //   dR/dyaw  = rows (-R row1, R row0, 0)
-__device__ inline void pose_from_theta(const double* __restrict__ th, Pose* __restrict__ P)
+__device__ inline void pose_from_sincos(const double* __restrict__ th, double sr, double cr, double sp, double cp,
+                                        double sy, double cy, Pose* __restrict__ P)
 {
 #pragma clang fp contract(off)
-    double sr, cr, sp, cp, sy, cy;
-    sincos(th[3], &sr, &cr);
-    sincos(th[4], &sp, &cp);
-    sincos(th[5], &sy, &cy);
     const double A0[3] = {cy * cp, sy * cp, -sp};
     const double A1[3] = {-sy, cy, 0.0};
     const double A2[3] = {cy * sp, sy * sp, cp};
@@ -47,6 +44,15 @@ __device__ inline void pose_from_theta(const double* __restrict__ th, Pose* __re
     for (int i = 0; i < 3; ++i) P->u[i] = th[i];
     for (int i = 0; i < 27; ++i) P->dR[i] = D[i];
     P->pad_ = 0.0;
+}
+
+__device__ inline void pose_from_theta(const double* __restrict__ th, Pose* __restrict__ P)
+{
+    double sr, cr, sp, cp, sy, cy;
+    sincos(th[3], &sr, &cr);
+    sincos(th[4], &sp, &cp);
+    sincos(th[5], &sy, &cy);
+    pose_from_sincos(th, sr, cr, sp, cp, sy, cy, P);
 }
 
 __global__ void pose_kernel(const double* __restrict__ theta, Pose* __restrict__ pose, int64_t n)

@@ -43,7 +43,7 @@ constexpr int kPhiThreads = 256;   // threads per particle of the direction / up
 __global__ __launch_bounds__(kPhiThreads) void svgd_phi_update_kernel(SvgdArgs a)
 {
     __shared__ double red[kPhiThreads / kWave][6];
-    __shared__ double tn_sh[6];
+    __shared__ double tn_sh[6], bc_sh[2], sn_sh[3], cs_sh[3];
     const int64_t p = blockIdx.y;
     const int K = a.K;
     const int tid = threadIdx.x;
@@ -70,11 +70,11 @@ __global__ __launch_bounds__(kPhiThreads) void svgd_phi_update_kernel(SvgdArgs a
         const int i = tid + u * kPhiThreads;
         sp0[u] = i < a.m ? a.src4[pd.src_off + srow[i]] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    double bc1 = 1.0, bc2 = 1.0;
-    if (tid < 6 && a.prm.optimizer != 1) {
+    // (by two lanes of the last wavefront, which has the fewest terms: the
+    // first one, which updates the particle, does not wait for the powers)
+    if (wave == kPhiThreads / kWave - 1 && lane < 2 && a.prm.optimizer != 1) {
         const double t_new = (double)(a.step[p] + 1);
-        bc1 = 1.0 - pow(a.prm.beta1, t_new);
-        bc2 = 1.0 - pow(a.prm.beta2, t_new);
+        bc_sh[lane] = 1.0 - pow(lane ? a.prm.beta2 : a.prm.beta1, t_new);
     }
 
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -106,12 +106,7 @@ __global__ __launch_bounds__(kPhiThreads) void svgd_phi_update_kernel(SvgdArgs a
         }
     }
 #pragma unroll
-    for (int d = 0; d < 6; ++d) {
-        double x = acc[d];
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        acc[d] = x;
-    }
+    for (int d = 0; d < 6; ++d) acc[d] = wave_sum(acc[d]);
     if (lane < 6) {
         double v = 0.0;
 #pragma unroll
@@ -138,12 +133,14 @@ __global__ __launch_bounds__(kPhiThreads) void svgd_phi_update_kernel(SvgdArgs a
             const double vv = a.prm.beta2 * a.vel[e] + (1.0 - a.prm.beta2) * (g * g);
             a.mom[e] = mm;
             a.vel[e] = vv;
-            const double mhat = mm / bc1;
-            const double vhat = vv / bc2;
+            const double mhat = mm / bc_sh[0];
+            const double vhat = vv / bc_sh[1];
             tnew = th[6 * k + tid] - a.prm.lr * mhat / (sqrt(vhat) + a.prm.eps);
         }
         a.theta_next[e] = tnew;
         tn_sh[tid] = tnew;
+        // the new angles' sines and cosines, a lane each
+        if (tid >= 3) sincos(tnew, &sn_sh[tid - 3], &cs_sh[tid - 3]);
     }
     __syncthreads();
     double tn[6];
@@ -152,7 +149,7 @@ __global__ __launch_bounds__(kPhiThreads) void svgd_phi_update_kernel(SvgdArgs a
     // the new pose (every thread computes the same bits) and this particle's
     // queries of the next iteration
     Pose P;
-    pose_from_theta(tn, &P);
+    pose_from_sincos(tn, sn_sh[0], cs_sh[0], sn_sh[1], cs_sh[1], sn_sh[2], cs_sh[2], &P);
     if (tid == 0) a.pose[p * K + k] = P;
     if (k == 0 && tid == 0) a.step_next[p] = a.step[p] + 1;   // read only by the next iteration
 #pragma unroll
