@@ -6,8 +6,8 @@
 // points (x, y, z, original index), level 1 one box per leaf, level l + 1 one
 // box per kFan boxes of level l, up to a level of at most kFan boxes. Every
 // level is padded to whole blocks of kFan entries: points by copies of a
-// point of their leaf, numbered kNoPoint, boxes by empty ones, which no query
-// can enter. Any
+// point of their leaf, numbered kNoPoint, boxes by empty ones (both corners at
+// infinity), which no query can enter. Any
 // order of the points gives a correct index; the order only decides how tight
 // the boxes are. (Morton order needs no splits but took 2 to 3.5 times the
 // blocks per query: 24.9 against 7.3 for the 100,000-point street scan.)
@@ -22,9 +22,10 @@
 //
 // Exactness: the FP32 distance of a point p of a box [lo, hi] is
 // fma(dz, dz, fma(dy, dy, dx dx)) with dx = fl(q - p). Rounding is monotone
-// and lo <= p <= hi, so |dx| >= max(fl(lo - q), fl(q - hi), 0), and products
-// and sums of non-negative terms keep the order: the same expression over
-// those three bounds never exceeds the point's distance, with no margin. A
+// and lo <= p <= hi, so |dx| >= |fl(q - c)| for the box's nearest coordinate
+// c = med(q, lo, hi), and products and sums of non-negative terms keep the
+// order: the same expression over those three differences never exceeds the
+// point's distance, with no margin. A
 // block is skipped only when its bound is larger than a distance that was
 // found, so the result is the smallest (distance, index) key of the whole
 // cloud, ties to the lowest index as in the brute-force search, bit for bit.
@@ -612,7 +613,7 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
             lo[e] = any ? from_order_bits(~v[3 + e]) : inf;
-            hi[e] = any ? from_order_bits(v[e]) : -inf;
+            hi[e] = any ? from_order_bits(v[e]) : inf;
         }
         put_box(a.nodes + d.level_off[level], box, lo, hi);
     };
@@ -652,15 +653,19 @@ __global__ __launch_bounds__(kIndexThreads) void index_upper_kernel(IndexBuildAr
         const int64_t padded = (real + kFan - 1) / kFan * kFan;
         for (int64_t e = (l == 3 ? real : 0) + threadIdx.x; e < padded; e += kIndexThreads) {
             const float inf = __builtin_inff();
-            float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
-            if (e < real) {   // the children are one block; padding boxes are empty
+            float lo[3] = {inf, inf, inf}, hi[3] = {inf, inf, inf};
+            if (e < real) {   // the children are one block, the first of them real
                 const float4* c = a.nodes + d.level_off[l - 1] + e * (kFan / 4 * kBoxQuad);
+                auto upper = [&](float x, float y) { return x == inf ? -inf : y; };   // of an empty box: none
+#pragma unroll
+                for (int f = 0; f < 3; ++f) hi[f] = -inf;
                 for (int u = 0; u < kFan / 4; ++u)
 #pragma unroll
                     for (int f = 0; f < 3; ++f) {
                         const float4 x = c[u * kBoxQuad + f], y = c[u * kBoxQuad + 3 + f];
                         lo[f] = fminf(lo[f], fminf(fminf(x.x, x.y), fminf(x.z, x.w)));
-                        hi[f] = fmaxf(hi[f], fmaxf(fmaxf(y.x, y.y), fmaxf(y.z, y.w)));
+                        hi[f] = fmaxf(hi[f], fmaxf(fmaxf(upper(x.x, y.x), upper(x.y, y.y)),
+                                                   fmaxf(upper(x.z, y.z), upper(x.w, y.w))));
                     }
             }
             put_box(a.nodes + d.level_off[l], e, lo, hi);
@@ -808,15 +813,21 @@ __global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_ke
         const uint32_t quad = block * (kFan / 4) + quad0;
         const uint32_t at = (uint32_t)level_off[level] + 16 * quad + (box ? 8 * quad : 0) + place;
         const Row<E>* src = (const Row<E>*)(nodes + at);
-        const Row<E>* up = (const Row<E>*)(nodes + at + (box ? 12 : 0));
-        const Row<E> lx = src[0], ly = src[4 / E], lz = src[8 / E], hx = up[0], hy = up[4 / E], hz = up[8 / E];
+        const Row<E> lx = src[0], ly = src[4 / E], lz = src[8 / E];
+        Row<E> hx = lx, hy = ly, hz = lz;   // of a point; a box's upper corner follows its lower one
+        const Row<E> fourth = src[12 / E];
+        if (box) {
+            hx = fourth;
+            hy = src[16 / E];
+            hz = src[20 / E];
+        }
         uint32_t cur[E];
 #pragma unroll
         for (int u = 0; u < E; ++u) {
 #pragma clang fp contract(off)
-            const float dx = __builtin_fmaxf(__builtin_fmaxf(lx.v[u] - q.x, q.x - hx.v[u]), 0.f);
-            const float dy = __builtin_fmaxf(__builtin_fmaxf(ly.v[u] - q.y, q.y - hy.v[u]), 0.f);
-            const float dz = __builtin_fmaxf(__builtin_fmaxf(lz.v[u] - q.z, q.z - hz.v[u]), 0.f);
+            const float dx = q.x - __builtin_amdgcn_fmed3f(q.x, lx.v[u], hx.v[u]);
+            const float dy = q.y - __builtin_amdgcn_fmed3f(q.y, ly.v[u], hy.v[u]);
+            const float dz = q.z - __builtin_amdgcn_fmed3f(q.z, lz.v[u], hz.v[u]);
             cur[u] = __float_as_uint(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
         }
         auto least = [&] {
@@ -836,7 +847,7 @@ __global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_ke
 #pragma unroll
             for (int u = 0; u < E; ++u) cur[u] = (cur[u] & ~kEntry) | (E * fl + u);
         } else {
-            const Row<E> id = src[12 / E];
+            const Row<E> id = fourth;
 #pragma unroll
             for (int u = 0; u < E; ++u) {
                 const uint64_t o = ((uint64_t)cur[u] << 32) | __float_as_uint(id.v[u]);
@@ -922,9 +933,9 @@ __global__ __launch_bounds__(search_threads(16)) void index_knn_kernel(IndexKnnA
         uint32_t cur;
         {
 #pragma clang fp contract(off)
-            const float dx = __builtin_fmaxf(__builtin_fmaxf(src[0] - qx, qx - up[0]), 0.f);
-            const float dy = __builtin_fmaxf(__builtin_fmaxf(src[4] - qy, qy - up[4]), 0.f);
-            const float dz = __builtin_fmaxf(__builtin_fmaxf(src[8] - qz, qz - up[8]), 0.f);
+            const float dx = qx - __builtin_amdgcn_fmed3f(qx, src[0], up[0]);
+            const float dy = qy - __builtin_amdgcn_fmed3f(qy, src[4], up[4]);
+            const float dz = qz - __builtin_amdgcn_fmed3f(qz, src[8], up[8]);
             cur = __float_as_uint(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
         }
         if (box) {
