@@ -2,7 +2,7 @@
 
 One step = one complete solve of the workload: reset the K particles and the
 Adam state to the seeded initial set, then run T iterations (minibatch,
-transform, brute-force nearest neighbours, mean gradients, Stein direction,
+transform, exact nearest neighbours, mean gradients, Stein direction,
 Adam), all on the GPU through the C ABI. Inputs are resident in HBM before
 the timed region. Prints one JSON line.
 
@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -127,6 +128,25 @@ def measure_ceilings():
     from paper_2106_03287_amd import peaks
     CEILINGS.update(peaks.measure())
     return {k: (round(v, 1) if isinstance(v, float) else v) for k, v in CEILINGS.items()}
+
+
+def index_roofline(queries, refs, nn_ms):
+    """The indexed search of a launch: the distances a balanced search cannot do
+    without, 8 flops a level and query over log2(refs) levels, on the FP32
+    vector units; the rate of brute-force pair evaluations it stands for
+    beside it. refs: references of each query's cloud, weighted by queries."""
+    t = nn_ms * 1e-3
+    flops = sum(n * FLOPS_PER_PAIR * max(1, math.ceil(math.log2(r))) for n, r in zip(queries, refs))
+    useful = flops / t / 1e12
+    pairs = sum(n * r for n, r in zip(queries, refs))
+    out = {"bound": "alu", "achieved": round(useful, 3), "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
+           "frac": round(useful / VALU_PEAK_TFLOPS, 4), "traffic": None, "avg_launch_ms": round(nn_ms, 5),
+           "flops_per_launch": flops, "kernel": "index_nn_kernel",
+           "brute_force_pair_evals_per_s": round(pairs / t, 1)}
+    if CEILINGS:
+        out["measured_peak"] = {"value": round(CEILINGS["fp32_fma_tflops"], 1), "unit": "TFLOP/s",
+                                "probe": "fp32_fma_tflops", "frac": round(useful / CEILINGS["fp32_fma_tflops"], 4)}
+    return out
 
 
 def nn_roofline(nn, pairs_per_launch, nn_ms, counters):
@@ -298,7 +318,7 @@ def cpu_kdtree_reference(prob, budget_s=10.0):
 # is latency-bound.
 AUTO_NN = {"cuboid": "fp32", "kinect": "f16", "lidar": "f16", "mc": "f16", "batched": "f16"}
 
-# NN shapes (queries per lane, wavefronts per workgroup, chunk, persistent
+# Brute-force NN shapes (queries per lane, wavefronts per workgroup, chunk, persistent
 # workgroups per CU) pinned from sweeps of the NN launch on one MI355X: LiDAR
 # FP16 x 2 1.22 ms with one chunk (1.24 with two, 1.44 with four), BF16 x 3
 # 1.64 ms with two (1.77 with four); Kinect one chunk of the whole reference.
@@ -332,7 +352,7 @@ def main():
                     help="do not query rocm-smi (a profiler that initialises the GPU before the program starts "
                          "forbids starting another program)")
     ap.add_argument("--autotune", type=int, default=0,
-                    help="tune the NN shape at init instead of using the pinned shape of the workload")
+                    help="(kept; without --tiling the context always tunes its search at init)")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="run one plain device copy of this size first (counter calibration)")
     ap.add_argument("--iters", type=int, default=0,
@@ -344,7 +364,8 @@ def main():
                     help="batched workload: skip the same pairs solved one after another (counter runs, whose "
                          "kernel records should hold the batched launches only)")
     ap.add_argument("--tiling", default="",
-                    help="force the NN shape 'queries_per_lane,waves,chunk[,persist]' instead of tuning")
+                    help="brute-force search of the mode in the shape 'queries_per_lane,waves,chunk[,persist]' (or "
+                         "'pinned', the workload's) instead of the context's indexed search")
     args = ap.parse_args()
     if args.gpus != 1:
         print(f"bench.py: this build runs on one GPU; --gpus {args.gpus} is not supported "
@@ -361,10 +382,10 @@ def main():
         args.ceilings = measure_ceilings()
     if args.nn == "auto":
         args.nn = AUTO_NN.get(args.workload, "fp32")
-    if not args.tiling and not args.autotune:
-        args.tiling = PINNED_TILING.get((args.workload, args.nn), "")
-        if not args.tiling:
-            args.autotune = 1
+    if args.tiling == "pinned":   # the brute-force search of the mode in its best shape
+        args.tiling = PINNED_TILING[(args.workload, args.nn)]
+    if not args.tiling:           # the context's own search: the index on every workload here
+        args.autotune = 1
     if args.copy_probe_mib:
         n = args.copy_probe_mib * (1 << 20) // 4
         a = torch.ones(n, dtype=torch.float32, device="cuda")
@@ -436,10 +457,11 @@ def main():
     stage = sol.stage_times(prob.T)
     nn_ms = sol.time_nn(max(20, min(200, int(200 / max(stage["nn"] / prob.T, 1e-3)))))
     pairs_per_launch = prob.K * prob.m * M
-    roofline = nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters(prob.name, tiling, args.nn))
+    roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters(prob.name, tiling, args.nn))
+                if args.tiling else index_roofline([prob.K * prob.m], [M], nn_ms))
     mismatch, identical = None, None
     if args.nn in SCREENS:
-        # against the FP32 search from the same state: the first iteration's
+        # against the brute-force FP32 search from the same state: the first iteration's
         # matches, and the particles after the whole solve (bit for bit)
         S.stein_icp_set_state(sol.ctx, theta0, zeros, zeros, 0)
         sol.step(1)
@@ -448,6 +470,7 @@ def main():
                                            schedule_rows=prob.schedule.shape[0], lr=prob.lr,
                                            metric=cfg.metric, normal_k=NORMAL_K)
         ref32 = S.SteinICP(cfg32, src, ref, theta0, sched)
+        ref32.set_tiling(*[int(x) for x in PINNED_TILING.get((args.workload, "fp32"), "2,4,1024,0").split(",")])
         ref32.step(1)
         mismatch = float((mb != ref32.diagnostics()["match"]).double().mean().item())
         solve()
@@ -468,7 +491,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": DTYPE[args.nn],
+        "dtype": DTYPE[args.nn] if args.tiling else "f32",   # the indexed search takes FP32 distances in every mode
         "data": "synthetic",
         "config": {"workload": prob.name, "K": prob.K, "m": prob.m, "T": prob.T,
                    "N": len(prob.pair.src), "M": M, "nn": args.nn, "metric": args.metric,
@@ -552,7 +575,8 @@ def run_batched(args):
     stage = batch.stage_times(T)
     nn_ms = batch.time_nn(20)
     pairs_per_launch = sum(K * m * len(p.pair.ref) for p in probs)
-    roofline = nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters("batched", tiling, args.nn))
+    roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters("batched", tiling, args.nn))
+                if args.tiling else index_roofline([K * m] * P, [len(p.pair.ref) for p in probs], nn_ms))
     value = P * T / (ms_b / 1e3)
     out = {
         "metric": METRIC,
@@ -565,7 +589,7 @@ def run_batched(args):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": DTYPE[args.nn],
+        "dtype": DTYPE[args.nn] if args.tiling else "f32",   # the indexed search takes FP32 distances in every mode
         "data": "synthetic",
         "config": {"workload": "batched", "pairs": P, "K": K, "m": m, "T": T,
                    "M_range": [min(len(p.pair.ref) for p in probs), max(len(p.pair.ref) for p in probs)],
@@ -624,7 +648,7 @@ def run_mc(args):
     scfg = S.stein_icp_default_config(num_particles=prob.K, batch_size=prob.m, schedule_rows=prob.schedule.shape[0],
                                       lr=prob.lr, nn_mode=nn_mode)
     stein = S.SteinICP(scfg, src, ref, dev(prob.theta0), dev(prob.schedule))
-    if nn in SCREENS:
+    if nn in SCREENS and args.tiling:
         stein.set_tiling(*[int(x) for x in PINNED_TILING[("kinect", nn)].split(",")])
     sz = torch.zeros_like(dev(prob.theta0))
 
@@ -664,7 +688,8 @@ def run_mc(args):
     tiling = mc.tiling()
     M = len(prob.pair.ref)
     pairs_per_launch = R * prob.m * M
-    roofline = nn_roofline(nn, pairs_per_launch, nn_ms, measured_counters("mc", tiling, nn))
+    roofline = (nn_roofline(nn, pairs_per_launch, nn_ms, measured_counters("mc", tiling, nn))
+                if args.tiling else index_roofline([R * prob.m], [M], nn_ms))
     r4 = lambda v: [round(float(x), 4) for x in v]  # noqa: E731
     out = {
         "metric": METRIC,
@@ -677,7 +702,7 @@ def run_mc(args):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": DTYPE[nn],
+        "dtype": DTYPE[nn] if args.tiling else "f32",
         "data": "synthetic",
         "config": {"workload": "mc", "pair": "kinect", "runs": R, "K": 1, "m": prob.m, "T": T, "M": M,
                    "start_box": [synth.MC_HALF_TRANS, synth.MC_HALF_ROT], "nn": nn,
@@ -803,7 +828,7 @@ def run_proposal(args):
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16 network, f16+f32 search and f64 Stein ICP (proposal); f32 search (plain)",
+        "dtype": "bf16 network, f32 search and f64 Stein ICP (proposal); f32 search (plain)",
         "data": "synthetic",
         "config": {"workload": "proposal", "pairs": n, "K": 100, "T_reference": T, "threshold": res["threshold"],
                    "nn_proposal": "f16", "nn_plain": "fp32",
