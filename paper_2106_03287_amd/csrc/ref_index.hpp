@@ -757,17 +757,19 @@ inline int pair_distance_blocks(int K, int threads) { return (2 * K * kWave + th
 // queries are ordered by minibatch point, then particle, so that those of a
 // wavefront look for (nearly) the same place and read the same blocks.
 //
-// Bound by the vector instructions and the latency of the dependent steps, 5
-// (2,000 references) to 8 (100,000) a query; the whole index stays in L2.
-// us a launch with 4 and with 16 lanes (what it replaced: the brute-force
-// search of the mode): 300,000 queries of 100,000 street references 63 and 85
-// (1,055), 64 uneven pairs of 30,000 queries 348 and 506 (1,114), 1,000 runs
-// of 300 queries of 20,000 68 and 80 (231), 30,000 of 20,000 tabletop 17.4
-// and 13.9 (34), 16,247 of 12,345 13.1 and 10.2 (85), 10,000 of 2,000 11.8
-// and 9.1 (9.9). Left out after measuring: upper levels staged in LDS
-// (slower throughout: the staging and the occupancy cost more than the
-// loads), a second query in turn per group (street 72 -> 82), fan-out 64 on
-// 16 lanes (tabletop 16.6, street 112) and 4 on one lane (41, 94).
+// Many queries are bound by the issue of their loads (a 16-byte load of a
+// wavefront takes 16 cycles of the compute unit's load path; 4 lanes a query
+// take the fewest), few ones by the latency of the dependent steps, 5 (2,000
+// references) to 8 (100,000) a query; the whole index stays in L2. us a launch
+// with 4 and with 16 lanes (what it replaced: the brute-force search of the
+// mode): 300,000 queries of 100,000 street references 56 and 85 (1,055), 64
+// uneven pairs of 30,000 queries 284 and 506 (1,114), 1,000 runs of 300
+// queries of 20,000 60 and 80 (231), 30,000 of 20,000 tabletop 17.4 and 13.9
+// (34), 16,247 of 12,345 13.1 and 10.2 (85), 10,000 of 2,000 11.8 and 9.1
+// (9.9). Left out after measuring: upper levels staged in LDS (street +0 to
+// 7 %, tabletop +4 %, 64 pairs -1 %: their loads are few), several queries in
+// turn per group (street 72 -> 82), fan-out 64 on 16 lanes (tabletop 16.6,
+// street 112) and 4 on one lane (41, 94).
 template <int L, bool BW>
 __global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_kernel(IndexSearchArgs a)
 {
