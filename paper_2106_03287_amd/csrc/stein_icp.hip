@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <set>
@@ -554,6 +555,64 @@ void launch_index_nn(int lanes, bool bw, int levels, int64_t nq, int64_t pairs, 
 }
 
 // Queries of the coming iteration from the current poses and step count.
+// Arrays of the context to a caller's device memory. A copy is a launch of
+// its own (about 2 us on the device, 4 us of the caller): one kernel takes up to
+// four where together they are at most 1 MB (a step of 10 particles with its
+// particles and diagnostics read back: 64 us with copies, 59 so). What
+// only a copy engine may write keeps the copies: memory that is not this
+// device's own, addresses off 4 bytes, overlapping arrays (then the last
+// wins), and larger ones, where the copies' wide loads count.
+struct OutArray {
+    void* dst;
+    const void* src;
+    size_t bytes;
+};
+
+hipError_t copy_out(const stein_icp_ctx* c, std::initializer_list<OutArray> arrays, hipStream_t s)
+{
+    OutArray a[4];
+    int n = 0;
+    size_t total = 0;
+    for (const OutArray& o : arrays)
+        if (o.dst) {
+            a[n++] = o;
+            total += o.bytes;
+        }
+    if (n == 0) return hipSuccess;
+    int dev = -1;
+    bool one = n > 1 && total <= ((size_t)1 << 20) && hipGetDevice(&dev) == hipSuccess && dev == c->device;
+    for (int i = 0; i < n && one; ++i) {
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, a[i].dst) != hipSuccess) {
+            (void)hipGetLastError();   // an address of the host's own
+            one = false;
+        }
+        one = one && (uintptr_t)a[i].dst % 4 == 0 && at.type == hipMemoryTypeDevice && at.device == c->device &&
+              !at.isManaged;
+        for (int j = 0; j < i && one; ++j)
+            one = (char*)a[i].dst >= (char*)a[j].dst + a[j].bytes || (char*)a[j].dst >= (char*)a[i].dst + a[i].bytes;
+    }
+    if (one) {
+        CopyOut k{};
+        uint32_t most = 0;
+        for (int i = 0; i < n; ++i) {
+            k.src[i] = (const uint32_t*)a[i].src;
+            k.dst[i] = (uint32_t*)a[i].dst;
+            k.words[i] = (uint32_t)(a[i].bytes / 4);
+            most = std::max(most, k.words[i]);
+        }
+        dim3 grid = grid1d(std::min<int64_t>(most, 256 * 256), 256);
+        grid.y = (unsigned)n;
+        hipLaunchKernelGGL(copy_out_kernel, grid, dim3(256), 0, s, k);
+        return hipGetLastError();
+    }
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = hipMemcpyAsync(a[i].dst, a[i].src, a[i].bytes, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t enqueue_queries(const stein_icp_ctx* c, hipStream_t s)
 {
     hipLaunchKernelGGL(queries_kernel, dim3((unsigned)ceil_div(c->nq, 256), (unsigned)c->P), dim3(256), 0, s,
@@ -1479,8 +1538,7 @@ int stein_icp_step(stein_icp_ctx* ctx, int32_t n_iters, void* hip_stream)
 int stein_icp_particles(const stein_icp_ctx* ctx, double* out, void* hip_stream)
 {
     if (!ctx || !out) return fail(STEIN_ICP_E_INVALID, "ctx or out is NULL");
-    HIP_TRY(hipMemcpyAsync(out, ctx->theta, 8 * (size_t)ctx->P * ctx->K * 6, hipMemcpyDeviceToDevice,
-                           (hipStream_t)hip_stream));
+    HIP_TRY(copy_out(ctx, {{out, ctx->theta, 8 * (size_t)ctx->P * ctx->K * 6}}, (hipStream_t)hip_stream));
     return STEIN_ICP_OK;
 }
 
@@ -1490,9 +1548,7 @@ int stein_icp_get_state(const stein_icp_ctx* ctx, double* theta, double* mom, do
     if (!ctx) return fail(STEIN_ICP_E_INVALID, "ctx is NULL");
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t bytes = 8 * (size_t)ctx->P * ctx->K * 6;
-    if (theta) HIP_TRY(hipMemcpyAsync(theta, ctx->theta, bytes, hipMemcpyDeviceToDevice, s));
-    if (mom) HIP_TRY(hipMemcpyAsync(mom, ctx->mom, bytes, hipMemcpyDeviceToDevice, s));
-    if (vel) HIP_TRY(hipMemcpyAsync(vel, ctx->vel, bytes, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(copy_out(ctx, {{theta, ctx->theta, bytes}, {mom, ctx->mom, bytes}, {vel, ctx->vel, bytes}}, s));
     int64_t tt = 0;
     HIP_TRY(hipMemcpyAsync(&tt, ctx->step, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -1500,36 +1556,42 @@ int stein_icp_get_state(const stein_icp_ctx* ctx, double* theta, double* mom, do
     return STEIN_ICP_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Every input is checked before anything of the context changes.
+template <typename T>
+int load_state(stein_icp_ctx* ctx, const T* theta, const T* mom, const T* vel, int64_t t, const char* what,
+               hipStream_t s)
+{
+    const int64_t part = (int64_t)ctx->P * ctx->K, n = part * 6;
+    const bool one_wg = n <= kCheckOneWg;
+    int bad = 0;
+    if (!one_wg) hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, ctx->flag, (int64_t)1, 0);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(check_state_kernel<T>), one_wg ? dim3(1) : grid1d(n, 1024), dim3(1024), 0, s,
+                       theta, mom, vel, n, ctx->flag);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(&bad, ctx->flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (bad) return fail(STEIN_ICP_E_INVALID, what);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(load_state_kernel<T>), grid1d(part, 64), dim3(64), 0, s, theta, mom, vel, t,
+                       part, (int64_t)ctx->P, ctx->theta, ctx->mom, ctx->vel, ctx->step, ctx->pose);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(enqueue_queries(ctx, s));
+    return STEIN_ICP_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int stein_icp_set_state(stein_icp_ctx* ctx, const double* theta, const double* mom, const double* vel, int64_t t,
                         void* hip_stream)
 {
     if (!ctx || !theta) return fail(STEIN_ICP_E_INVALID, "ctx or theta is NULL");
     if (t < 0) return fail(STEIN_ICP_E_INVALID, "t must be >= 0");
-    hipStream_t s = (hipStream_t)hip_stream;
-    const int64_t n = (int64_t)ctx->P * ctx->K * 6;
-    // every input is checked before anything of the context changes
-    {
-        int bad = 0;
-        hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, ctx->flag, (int64_t)1, 0);
-        hipLaunchKernelGGL(check_finite_kernel, grid1d(n, 256), dim3(256), 0, s, theta, n, ctx->flag);
-        if (mom) hipLaunchKernelGGL(check_finite_kernel, grid1d(n, 256), dim3(256), 0, s, mom, n, ctx->flag);
-        if (vel) hipLaunchKernelGGL(check_finite_kernel, grid1d(n, 256), dim3(256), 0, s, vel, n, ctx->flag);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(&bad, ctx->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (bad) return fail(STEIN_ICP_E_INVALID, "a particle or moment is non-finite");
-    }
-    HIP_TRY(hipMemcpyAsync(ctx->theta, theta, 8 * n, hipMemcpyDeviceToDevice, s));
-    if (mom) HIP_TRY(hipMemcpyAsync(ctx->mom, mom, 8 * n, hipMemcpyDeviceToDevice, s));
-    else hipLaunchKernelGGL(fill_f64_kernel, grid1d(n, 256), dim3(256), 0, s, ctx->mom, n, 0.0);
-    if (vel) HIP_TRY(hipMemcpyAsync(ctx->vel, vel, 8 * n, hipMemcpyDeviceToDevice, s));
-    else hipLaunchKernelGGL(fill_f64_kernel, grid1d(n, 256), dim3(256), 0, s, ctx->vel, n, 0.0);
-    hipLaunchKernelGGL(fill_i64_kernel, grid1d(ctx->P, 256), dim3(256), 0, s, ctx->step, (int64_t)ctx->P, t);
-    hipLaunchKernelGGL(pose_kernel, grid1d((int64_t)ctx->P * ctx->K, 256), dim3(256), 0, s, ctx->theta, ctx->pose,
-                       (int64_t)ctx->P * ctx->K);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(enqueue_queries(ctx, s));
-    return STEIN_ICP_OK;
+    return load_state(ctx, theta, mom, vel, t, "a particle or moment is non-finite", (hipStream_t)hip_stream);
 }
 
 int stein_icp_particles_f32(const stein_icp_ctx* ctx, float* out, void* hip_stream)
@@ -1544,24 +1606,7 @@ int stein_icp_particles_f32(const stein_icp_ctx* ctx, float* out, void* hip_stre
 int stein_icp_set_particles_f32(stein_icp_ctx* ctx, const float* theta, void* hip_stream)
 {
     if (!ctx || !theta) return fail(STEIN_ICP_E_INVALID, "ctx or theta is NULL");
-    hipStream_t s = (hipStream_t)hip_stream;
-    const int64_t n = (int64_t)ctx->P * ctx->K * 6;
-    int bad = 0;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, ctx->flag, (int64_t)1, 0);
-    hipLaunchKernelGGL(check_finite_f32_kernel, grid1d(n, 256), dim3(256), 0, s, theta, n, ctx->flag);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(&bad, ctx->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (bad) return fail(STEIN_ICP_E_INVALID, "a particle is non-finite");
-    hipLaunchKernelGGL(widen_f32_kernel, grid1d(n, 256), dim3(256), 0, s, theta, n, ctx->theta);
-    hipLaunchKernelGGL(fill_f64_kernel, grid1d(n, 256), dim3(256), 0, s, ctx->mom, n, 0.0);
-    hipLaunchKernelGGL(fill_f64_kernel, grid1d(n, 256), dim3(256), 0, s, ctx->vel, n, 0.0);
-    hipLaunchKernelGGL(fill_i64_kernel, grid1d(ctx->P, 256), dim3(256), 0, s, ctx->step, (int64_t)ctx->P, (int64_t)0);
-    hipLaunchKernelGGL(pose_kernel, grid1d((int64_t)ctx->P * ctx->K, 256), dim3(256), 0, s, ctx->theta, ctx->pose,
-                       (int64_t)ctx->P * ctx->K);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(enqueue_queries(ctx, s));
-    return STEIN_ICP_OK;
+    return load_state<float>(ctx, theta, nullptr, nullptr, 0, "a particle is non-finite", (hipStream_t)hip_stream);
 }
 
 int stein_icp_get_diagnostics(const stein_icp_ctx* ctx, double* gbar, double* phi, double* h, int32_t* match,
@@ -1570,10 +1615,12 @@ int stein_icp_get_diagnostics(const stein_icp_ctx* ctx, double* gbar, double* ph
     if (!ctx) return fail(STEIN_ICP_E_INVALID, "ctx is NULL");
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t b6 = 8 * (size_t)ctx->P * ctx->K * 6;
-    if (gbar) HIP_TRY(hipMemcpyAsync(gbar, ctx->gbar, b6, hipMemcpyDeviceToDevice, s));
-    if (phi) HIP_TRY(hipMemcpyAsync(phi, ctx->phi, b6, hipMemcpyDeviceToDevice, s));
-    if (h) HIP_TRY(hipMemcpyAsync(h, ctx->h, 16 * (size_t)ctx->P, hipMemcpyDeviceToDevice, s));
-    if (match) HIP_TRY(hipMemcpyAsync(match, ctx->match, 4 * (size_t)ctx->P * ctx->nq, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(copy_out(ctx,
+                     {{gbar, ctx->gbar, b6},
+                      {phi, ctx->phi, b6},
+                      {h, ctx->h, 16 * (size_t)ctx->P},
+                      {match, ctx->match, 4 * (size_t)ctx->P * ctx->nq}},
+                     s));
     return STEIN_ICP_OK;
 }
 
