@@ -95,7 +95,8 @@ int make_scales(int32_t ns, const double* sigma, MmdScales& sc)
 
 int launch_gemm(hipStream_t s, int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                 const float* B, int64_t ldb, float* C, int64_t ldc, const float* bias, int relu, int acc,
-                int32_t splits, float* ws, unsigned long long* pool_keys = nullptr, int64_t pool_P = 0)
+                int32_t splits, float* ws, const float* gate = nullptr, unsigned long long* pool_keys = nullptr,
+                int64_t pool_P = 0)
 {
     if (M <= 0 || N <= 0) return STEIN_ICP_OK;
     if (splits < 1) splits = 1;
@@ -122,6 +123,7 @@ int launch_gemm(hipStream_t s, int ta, int tb, int64_t M, int64_t N, int64_t K, 
         g.C = C;
         g.ldc = ldc;
         g.bias = bias;
+        g.gate = gate;
         g.relu = relu;
         g.accumulate = acc;
         g.c_split = 0;
@@ -134,8 +136,8 @@ int launch_gemm(hipStream_t s, int ta, int tb, int64_t M, int64_t N, int64_t K, 
         g.accumulate = 0;
         g.c_split = M * N;
         gemm_bf16_kernel<<<grid, 256, 0, s>>>(g);
-        splitk_reduce_kernel<<<(unsigned)ceil_div(M * N, 256), 256, 0, s>>>(ws, splits, M, N, C, ldc, bias, relu,
-                                                                            acc);
+        splitk_reduce_kernel<<<(unsigned)ceil_div(M * N, 256), 256, 0, s>>>(ws, splits, M, N, C, ldc, bias, gate,
+                                                                            relu, acc);
     }
     HIP_TRY(hipGetLastError());
     return STEIN_ICP_OK;
@@ -168,7 +170,8 @@ namespace {
 using Model = stein_icp_proposal;
 
 int gemm(const Model* m, hipStream_t s, int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A,
-         int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, const float* bias, int relu)
+         int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, const float* bias, int relu,
+         const float* gate = nullptr)
 {
     // split K when the output tiles alone cannot fill the chip and K is long
     const int64_t tiles = ceil_div(M, kGT) * ceil_div(N, kGT);
@@ -179,16 +182,37 @@ int gemm(const Model* m, hipStream_t s, int ta, int tb, int64_t M, int64_t N, in
         splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>({want, by_k, kMaxSplits,
                                                                   m->ws_floats / std::max<int64_t>(M * N, 1)}));
     }
-    return launch_gemm(s, ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, relu, 0, splits, m->ws);
+    return launch_gemm(s, ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, relu, 0, splits, m->ws, gate);
 }
 
-int colsum(const Model* m, hipStream_t s, const float* X, int64_t rows, int64_t N, float* out)
+struct ColMat {
+    const float* X;
+    int64_t rows, N;
+    float* out;
+};
+
+int colsums(const Model* m, hipStream_t s, const ColMat (&mats)[kColMats])
 {
-    const int64_t nch = std::max<int64_t>(ceil_div(rows, kColChunk), 1);
-    if (nch * N > m->colpart_floats) return fail(STEIN_ICP_E_INVALID, "column-sum workspace too small");
-    colsum_partial_kernel<<<dim3((unsigned)ceil_div(N, 256), (unsigned)nch), 256, 0, s>>>(X, rows, N, kColChunk,
-                                                                                          m->colpart);
-    colsum_merge_kernel<<<(unsigned)ceil_div(N, 256), 256, 0, s>>>(m->colpart, nch, N, out);
+    ColSums a{};
+    a.chunk = kColChunk;
+    a.n = kColMats;
+    int64_t first = 0, mfirst = 0, part = 0;
+    for (int i = 0; i < kColMats; ++i) {
+        const int64_t nch = ceil_div(mats[i].rows, kColChunk), nb = ceil_div(mats[i].N, 256);
+        a.X[i] = mats[i].X;
+        a.out[i] = mats[i].out;
+        a.part[i] = m->colpart + part;
+        a.rows[i] = mats[i].rows;
+        a.N[i] = mats[i].N;
+        a.first[i] = (uint32_t)first;
+        a.mfirst[i] = (uint32_t)mfirst;
+        first += nch * nb;
+        mfirst += nb;
+        part += nch * mats[i].N;
+    }
+    if (part > m->colpart_floats) return fail(STEIN_ICP_E_INVALID, "column-sum workspace too small");
+    colsum_partial_kernel<<<(unsigned)first, 256, 0, s>>>(a);
+    colsum_merge_kernel<<<(unsigned)mfirst, 256, 0, s>>>(a);
     HIP_TRY(hipGetLastError());
     return STEIN_ICP_OK;
 }
@@ -253,32 +277,29 @@ int backward(Model* m, hipStream_t s, const float* X, int64_t B)
     const int64_t K6 = 6 * m->K, rows = 2 * B * kF3;
     // head: y = z W5 + b5, z = relu(f W4 + b4)
     CHECK(gemm(m, s, 1, 0, kFz, K6, B, m->Z, kFz, m->dY, K6, g + L.W5, K6, nullptr, 0));
-    CHECK(colsum(m, s, m->dY, B, K6, g + L.b5));
-    CHECK(gemm(m, s, 0, 1, B, kFz, K6, m->dY, K6, w + L.W5, K6, m->dZ, kFz, nullptr, 0));
-    relu_backward_kernel<<<(unsigned)ceil_div(B * kFz, 256), 256, 0, s>>>(m->Z, m->dZ, B * kFz);
+    CHECK(gemm(m, s, 0, 1, B, kFz, K6, m->dY, K6, w + L.W5, K6, m->dZ, kFz, nullptr, 0, m->Z));
     CHECK(gemm(m, s, 1, 0, kFcat, kFz, B, m->F, kFcat, m->dZ, kFz, g + L.W4, kFz, nullptr, 0));
-    CHECK(colsum(m, s, m->dZ, B, kFz, g + L.b4));
     CHECK(gemm(m, s, 0, 1, B, kFcat, kFz, m->dZ, kFz, w + L.W4, kFz, m->dF, kFcat, nullptr, 0));
     // winner rows: the winning points' inputs and the pooled gradients they
     // carry; their first two layers are recomputed with the forward's
     // products (one K slice each, the same MFMA order, bias and ReLU: the
     // same bits)
-    winner_rows_kernel<kF3><<<(unsigned)(2 * B), kF3, 0, s>>>(X, m->arg, m->F, m->dF, kFcat, m->P, m->G0, m->dA3);
+    winner_rows_kernel<kF3><<<dim3((unsigned)(2 * B), kWinnerParts), kF3, 0, s>>>(X, m->arg, m->F, m->dF, kFcat, m->P, m->G0, m->dA3);
     HIP_TRY(hipGetLastError());
     CHECK(launch_gemm(s, 0, 0, rows, kF1, 3, m->G0, 3, w + L.W1, kF1, m->G1, kF1, w + L.b1, 1, 0, 1, nullptr));
     CHECK(launch_gemm(s, 0, 0, rows, kF2, kF1, m->G1, kF1, w + L.W2, kF2, m->G2, kF2, w + L.b2, 1, 0, 1, nullptr));
     CHECK(gemm(m, s, 1, 0, kF2, kF3, rows, m->G2, kF2, m->dA3, kF3, g + L.W3, kF3, nullptr, 0));
-    CHECK(colsum(m, s, m->dA3, rows, kF3, g + L.b3));
-    CHECK(gemm(m, s, 0, 1, rows, kF2, kF3, m->dA3, kF3, w + L.W3, kF3, m->dA2, kF2, nullptr, 0));
-    relu_backward_kernel<<<(unsigned)ceil_div(rows * kF2, 256), 256, 0, s>>>(m->G2, m->dA2, rows * kF2);
+    CHECK(gemm(m, s, 0, 1, rows, kF2, kF3, m->dA3, kF3, w + L.W3, kF3, m->dA2, kF2, nullptr, 0, m->G2));
     CHECK(gemm(m, s, 1, 0, kF1, kF2, rows, m->G1, kF1, m->dA2, kF2, g + L.W2, kF2, nullptr, 0));
-    CHECK(colsum(m, s, m->dA2, rows, kF2, g + L.b2));
-    CHECK(gemm(m, s, 0, 1, rows, kF1, kF2, m->dA2, kF2, w + L.W2, kF2, m->dA1, kF1, nullptr, 0));
-    relu_backward_kernel<<<(unsigned)ceil_div(rows * kF1, 256), 256, 0, s>>>(m->G1, m->dA1, rows * kF1);
+    CHECK(gemm(m, s, 0, 1, rows, kF1, kF2, m->dA2, kF2, w + L.W2, kF2, m->dA1, kF1, nullptr, 0, m->G1));
     CHECK(gemm(m, s, 1, 0, 3, kF1, rows, m->G0, 3, m->dA1, kF1, g + L.W1, kF1, nullptr, 0));
-    CHECK(colsum(m, s, m->dA1, rows, kF1, g + L.b1));
-    HIP_TRY(hipGetLastError());
-    return STEIN_ICP_OK;
+    // every bias gradient at the end, where its operand still stands
+    return colsums(m, s,
+                   {{m->dY, B, K6, g + L.b5},
+                    {m->dZ, B, kFz, g + L.b4},
+                    {m->dA3, rows, kF3, g + L.b3},
+                    {m->dA2, rows, kF2, g + L.b2},
+                    {m->dA1, rows, kF1, g + L.b1}});
 }
 
 // `parts` workgroups a sample; part: B x parts doubles (loss itself for one).
@@ -350,7 +371,7 @@ int stein_icp_proposal_create(stein_icp_proposal** out, const stein_icp_proposal
     // split-K partials: the largest weight gradient product is W5 (256 x 6K)
     // or W4 (512 x 256); the per-point weights are smaller
     m->ws_floats = (int64_t)kMaxSplits * std::max<int64_t>({(int64_t)kFz * K6, (int64_t)kFcat * kFz, kF2 * kF3});
-    m->colpart_floats = std::max<int64_t>(ceil_div(std::max(slots, m->Bmax), kColChunk), 1) * std::max<int64_t>(K6, kF3);
+    m->colpart_floats = ceil_div(m->Bmax, kColChunk) * (K6 + kFz) + ceil_div(slots, kColChunk) * (kF3 + kF2 + kF1);
     // arena layout (256-byte aligned blocks)
     size_t off = 0;
     auto take = [&](size_t bytes) {

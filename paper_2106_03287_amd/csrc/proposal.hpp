@@ -31,6 +31,8 @@ __device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast
 
 // ------------------------------------------------------------------- GEMM
 // C = op(A) op(B) [+ bias] [ReLU] [+ C]   (M x N, FP32, row-major, ldc)
+// and, with `gate` (M x N, as C), zero where gate is not > 0: the backward of
+// the ReLU that produced it (a pass of its own took 1.8 to 5.7 us)
 //   op(A) = A   with A row-major M x K (lda)   when ta == 0,
 //         = A^T with A row-major K x M (lda)   when ta == 1;
 //   op(B) = B   with B row-major K x N (ldb)   when tb == 0,
@@ -50,6 +52,7 @@ struct GemmArgs {
     const float* B;
     float* C;
     const float* bias;
+    const float* gate;
     int64_t M, N, K, lda, ldb, ldc;
     int64_t kper, c_split;
     int32_t ta, tb, relu, accumulate;
@@ -214,6 +217,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
                     float v = acc[a][b][t];
                     if (g.bias) v += g.bias[gn];
                     if (g.relu) v = fmaxf(v, 0.f);
+                    if (g.gate && !(g.gate[gm * g.ldc + gn] > 0.f)) v = 0.f;
                     float* dst = Cz + gm * g.ldc + gn;
                     *dst = g.accumulate ? *dst + v : v;
                 }
@@ -447,10 +451,10 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_pool_kernel(MlpArgs g)
     if (cloud >= 0) flush();
 }
 
-// C[m][n] (+)= sum_{z < S} W[z][m][n] (+ bias[n]) (ReLU), z in order.
+// C[m][n] (+)= sum_{z < S} W[z][m][n] (+ bias[n]) (ReLU) (gate), z in order.
 __global__ void splitk_reduce_kernel(const float* __restrict__ W, int32_t S, int64_t M, int64_t N,
                                      float* __restrict__ C, int64_t ldc, const float* __restrict__ bias,
-                                     int32_t relu, int32_t accumulate)
+                                     const float* __restrict__ gate, int32_t relu, int32_t accumulate)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= M * N) return;
@@ -460,6 +464,7 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ W, int32_t S, int
     for (int32_t z = 0; z < S; ++z) s += W[(int64_t)z * M * N + i];
     if (bias) s += bias[n];
     if (relu) s = fmaxf(s, 0.f);
+    if (gate && !(gate[m * ldc + n] > 0.f)) s = 0.f;
     float* dst = C + m * ldc + n;
     *dst = accumulate ? *dst + s : s;
 }
@@ -531,7 +536,14 @@ __global__ void pool_keys_finish_kernel(const unsigned long long* __restrict__ k
 // features it wins (dA3[u][f] = dF[c][f] where F[c][f] > 0, else 0): the
 // dense backward's nonzero rows, so every product below is the dense chain
 // rule's product restricted to them (zero rows add exact zeros).
-// grid: clouds; F3 threads, one per feature.
+// grid: (clouds, kWinnerParts): the workgroups of a cloud number its winners
+// alike and write a share of the rows each. F3 threads: one per feature to
+// number, then four features of one row per 16-byte store (every element is
+// written once, value or zero). Bound by its stores, 16 MB at 32 pairs: 11.6 us
+// there; 33.5 with one workgroup a cloud, 4-byte stores and a serial search
+// for the first feature.
+constexpr int kWinnerParts = 4;
+
 template <int F3>
 __global__ __launch_bounds__(F3) void winner_rows_kernel(const float* __restrict__ X, const int32_t* __restrict__ arg,
                                                          const float* __restrict__ F, const float* __restrict__ dF,
@@ -539,83 +551,112 @@ __global__ __launch_bounds__(F3) void winner_rows_kernel(const float* __restrict
                                                          float* __restrict__ dA3)
 {
     constexpr int kW = 64;   // wavefront width
-    static_assert(F3 % kW == 0, "one thread per feature, whole wavefronts");
-    __shared__ int32_t pt[F3];
-    __shared__ int32_t row_of[F3];
+    constexpr int kRows = F3 / kWinnerParts, kQuads = F3 / 4;
+    static_assert(F3 % kW == 0 && kRows % 4 == 0, "one thread per feature, whole wavefronts; four rows a pass");
+    __shared__ __attribute__((aligned(16))) int32_t pt[F3];
+    __shared__ __attribute__((aligned(16))) int32_t row[F3];
+    __shared__ __attribute__((aligned(16))) float val[F3];
     __shared__ int32_t wtot[F3 / kW];
     const int64_t c = blockIdx.x;
     const int f = threadIdx.x, lane = f % kW, wv = f / kW;
     const int32_t p = min(max(arg[c * F3 + f], 0), (int32_t)(P - 1));   // arg is in range; clamp anyway
     pt[f] = p;
+    const int64_t e = (c / 2) * ld_f + (c % 2) * F3 + f;
+    val[f] = F[e] > 0.f ? dF[e] : 0.f;
     __syncthreads();
     int first = f;   // first feature won by the same point
-    for (int j = 0; j < f; ++j)
-        if (pt[j] == p) {
-            first = j;
-            break;
-        }
+#pragma unroll 8
+    for (int j = kQuads - 1; j >= 0; --j) {
+        const int4 q = reinterpret_cast<const int4*>(pt)[j];
+        first = q.w == p ? 4 * j + 3 : first;
+        first = q.z == p ? 4 * j + 2 : first;
+        first = q.y == p ? 4 * j + 1 : first;
+        first = q.x == p ? 4 * j : first;
+    }
     const bool owner = first == f;
     const unsigned long long ob = __ballot(owner);
-    const int before = __popcll(ob & ((1ull << lane) - 1ull));
     if (lane == 0) wtot[wv] = __popcll(ob);
     __syncthreads();
-    int r = before, rows = 0;
+    int r = __popcll(ob & ((1ull << lane) - 1ull)), rows = 0;
     for (int w = 0; w < F3 / kW; ++w) {
         r += w < wv ? wtot[w] : 0;
         rows += wtot[w];
     }
-    if (owner) row_of[f] = r;
-    float* __restrict__ Dc = dA3 + c * F3 * F3;
-    for (int e = f; e < F3 * F3; e += F3) Dc[e] = 0.f;
+    if (owner) row[f] = r;
+    __syncthreads();
+    const int mine = row[first];
+    __syncthreads();
+    row[f] = mine;   // the row of every feature, not of the owners only
+    const int r0 = (int)blockIdx.y * kRows, r1 = r0 + kRows;
     float* __restrict__ Gc = G0 + c * F3 * 3;
-    if (owner) {
+    if (owner && r >= r0 && r < r1) {
         const float* x = X + (c * P + p) * 3;
         Gc[3 * r] = x[0];
         Gc[3 * r + 1] = x[1];
         Gc[3 * r + 2] = x[2];
     }
-    if (f >= rows) Gc[3 * f] = Gc[3 * f + 1] = Gc[3 * f + 2] = 0.f;
-    __syncthreads();   // the zeros and row_of before the scatter
-    const int64_t e = (c / 2) * ld_f + (c % 2) * F3 + f;
-    Dc[(int64_t)row_of[first] * F3 + f] = F[e] > 0.f ? dF[e] : 0.f;
+    if (f >= rows && f >= r0 && f < r1) Gc[3 * f] = Gc[3 * f + 1] = Gc[3 * f + 2] = 0.f;
+    __syncthreads();
+    const int q = f % kQuads;
+    const int4 rq = reinterpret_cast<const int4*>(row)[q];
+    const float4 vq = reinterpret_cast<const float4*>(val)[q];
+    float4* __restrict__ Dc = reinterpret_cast<float4*>(dA3 + c * F3 * F3);
+    for (int u = r0 + f / kQuads; u < r1; u += 4)
+        Dc[u * kQuads + q] = make_float4(rq.x == u ? vq.x : 0.f, rq.y == u ? vq.y : 0.f, rq.z == u ? vq.z : 0.f,
+                                         rq.w == u ? vq.w : 0.f);
 }
 
 // ------------------------------------------------------------ elementwise
-// dA = dH where H > 0, else 0 (in place; H is the ReLU output).
-__global__ void relu_backward_kernel(const float* __restrict__ H, float* __restrict__ dH, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && !(H[i] > 0.f)) dH[i] = 0.f;
-}
-
 __global__ void fill_f32_kernel(float* __restrict__ x, int64_t n, float v)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) x[i] = v;
 }
 
-// Column sums of X (rows x N) in two fixed-order stages: partial sums over
-// row chunks (grid (ceil(N / 256), chunks)), then over chunks.
-__global__ void colsum_partial_kernel(const float* __restrict__ X, int64_t rows, int64_t N, int64_t chunk,
-                                      float* __restrict__ part)
+// Column sums of several matrices X (rows x N) in two launches of fixed-order
+// stages: partial sums over row chunks, then over chunks. A workgroup takes
+// 256 columns of one chunk; it finds its matrix by the first workgroups of
+// each (a launch of either stage per matrix, ten a training step, took 3 us
+// each; the two take 13.5 together at 32 pairs).
+constexpr int kColMats = 5;
+struct ColSums {
+    const float* X[kColMats];
+    float* out[kColMats];
+    float* part[kColMats];
+    int64_t rows[kColMats], N[kColMats];
+    uint32_t first[kColMats];    // first workgroup of the partial sums
+    uint32_t mfirst[kColMats];   // and of the merge
+    int64_t chunk;
+    int32_t n;
+};
+
+__global__ void colsum_partial_kernel(ColSums a)
 {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int i = a.n - 1;
+    while (i > 0 && blockIdx.x < a.first[i]) --i;
+    const float* __restrict__ X = a.X[i];
+    const int64_t N = a.N[i], nb = (N + 255) / 256, b = blockIdx.x - a.first[i];
+    const int64_t n = (b % nb) * 256 + threadIdx.x, ch = b / nb;
     if (n >= N) return;
-    const int64_t r0 = (int64_t)blockIdx.y * chunk, r1 = min(rows, r0 + chunk);
+    const int64_t r0 = ch * a.chunk, r1 = min(a.rows[i], r0 + a.chunk);
     float s = 0.f;
 #pragma unroll 16   // loads in flight; the sum keeps its order
     for (int64_t r = r0; r < r1; ++r) s += X[r * N + n];
-    part[(int64_t)blockIdx.y * N + n] = s;
+    a.part[i][ch * N + n] = s;
 }
 
-__global__ void colsum_merge_kernel(const float* __restrict__ part, int64_t nch, int64_t N, float* __restrict__ out)
+__global__ void colsum_merge_kernel(ColSums a)
 {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int i = a.n - 1;
+    while (i > 0 && blockIdx.x < a.mfirst[i]) --i;
+    const float* __restrict__ part = a.part[i];
+    const int64_t N = a.N[i], nch = (a.rows[i] + a.chunk - 1) / a.chunk;
+    const int64_t n = (int64_t)(blockIdx.x - a.mfirst[i]) * 256 + threadIdx.x;
     if (n >= N) return;
     float s = 0.f;
 #pragma unroll 32   // loads in flight; the sum keeps its order
     for (int64_t c = 0; c < nch; ++c) s += part[c * N + n];
-    out[n] = s;
+    a.out[i][n] = s;
 }
 
 // ------------------------------------------------------------- set loss

@@ -61,3 +61,33 @@ def test_stand_alone_set_distance_in_passes(K):
     got = PR.stein_icp_proposal_mmd(T._cuda(X, torch.float64), T._cuda(Y, torch.float64), sigma).cpu().numpy()
     want = np.array([PO.mmd2(X[b], Y[b], sigma) for b in range(2)])
     np.testing.assert_allclose(got, want, rtol=0, atol=1e-12)
+
+
+def euler_gaps(params, grad, K):
+    """A layer y = x W + b below a ReLU gate passes sum(y dy) = <W, gW> + <b, gb> down as sum(x dx) = <W, gW>: for
+    each pair of layers the difference of both forms, and the summed magnitudes of its terms."""
+    out = {}
+    dot = {n: params[o:o + int(np.prod(s))] * grad[o:o + int(np.prod(s))] for n, (o, s) in PO.layout(K).items()}
+    for lower, upper in ((1, 2), (2, 3), (3, 4), (4, 5)):
+        terms = [dot[f"W{lower}"], dot[f"b{lower}"], -dot[f"W{upper}"]]
+        out[f"{lower}-{upper}"] = (abs(sum(t.sum() for t in terms)), sum(np.abs(t).sum() for t in terms))
+    return out
+
+
+@pytest.mark.parametrize("P,B", [(1, 1), (8, 3), (64, 2), (300, 5), (1088, 33)])
+def test_gradients_agree_between_layers(P, B):
+    """Winner rows from one to all shares of a cloud, gates inside the products, bias sums of all layers at once.
+    Four BF16 operands stand between the two forms, 2^-8 relative each: 2^-6 of the summed magnitudes. A row, a gate
+    or a sum out of place changes a form by an amount of its own size."""
+    K = 8
+    params = T._params(K, 51)
+    targets = np.random.default_rng(52).standard_normal((B, K, 6)) * 0.3
+    sigma = np.array([[0.1] * 3 + [0.2] * 3, [0.4] * 3 + [0.8] * 3])
+    cfg = PR.stein_icp_proposal_default_config(num_particles=K, points=P, max_batch=B + 2, loss_sigma=sigma)
+    m = PR.Proposal(cfg, params)
+    _, grad = m.loss(T._cuda(T._clouds(B, P, 53)), T._cuda(targets, torch.float64), grad=True)
+    grad = grad.cpu().numpy().astype(np.float64)
+    m.close()
+    assert np.isfinite(grad).all()
+    for layers, (gap, size) in euler_gaps(np.asarray(params, np.float64), grad, K).items():
+        assert gap <= 2.0 ** -6 * size, layers
