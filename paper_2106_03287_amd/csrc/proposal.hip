@@ -118,7 +118,11 @@ int launch_gemm(hipStream_t s, int ta, int tb, int64_t M, int64_t N, int64_t K, 
     g.pool_P = pool_P;
     if (pool_keys) splits = 1;
     const int64_t Mt = ceil_div(M, kGT), Nt = ceil_div(N, kGT);
-    const dim3 grid((unsigned)(ceil_div(Mt, kXcds) * kXcds * Nt), 1, (unsigned)splits);
+    dim3 grid((unsigned)(ceil_div(Mt, kXcds) * kXcds * Nt), 1, (unsigned)splits);
+    const int64_t by_slice = ceil_div(splits, kXcds) * kXcds * Mt * Nt;
+    g.by_slice = Mt < kXcds && splits >= kXcds && by_slice < ((int64_t)1 << 20);
+    g.splits = splits;
+    if (g.by_slice) grid = dim3((unsigned)by_slice, 1, 1);
     if (splits == 1) {
         g.C = C;
         g.ldc = ldc;

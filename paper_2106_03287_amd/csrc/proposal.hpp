@@ -37,7 +37,7 @@ __device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast
 //         = A^T with A row-major K x M (lda)   when ta == 1;
 //   op(B) = B   with B row-major K x N (ldb)   when tb == 0,
 //         = B^T with B row-major N x K (ldb)   when tb == 1.
-// Split K: workgroup z covers K range [z kper, (z + 1) kper) and writes its
+// Split K: slice z covers K range [z kper, (z + 1) kper) and writes its
 // partial product, without bias, ReLU or accumulation, to C + z c_split
 // (the caller then sums the splits with splitk_reduce_kernel).
 // Pooled epilogue (pool_keys != nullptr, one K slice, ReLU on, rows in
@@ -55,7 +55,7 @@ struct GemmArgs {
     const float* gate;
     int64_t M, N, K, lda, ldb, ldc;
     int64_t kper, c_split;
-    int32_t ta, tb, relu, accumulate;
+    int32_t ta, tb, relu, accumulate, by_slice, splits;
     unsigned long long* pool_keys;
     int64_t pool_P;
 };
@@ -66,12 +66,26 @@ constexpr int kLdsPad = 8; // BF16 pad per LDS row: spreads banks, keeps 16-byte
 
 constexpr int kXcds = 8;   // workgroups are dealt to the 8 XCDs round robin
 
-// Tile of workgroup b in a 1-D grid of ceil(Mt / 8) * 8 * Nt workgroups
-// (Mt, Nt: row and column tiles). Workgroups b, b + 8, b + 16, ... land on
-// the same XCD; they are given the Nt column tiles of one row tile, so the
-// A rows they share are read once into that XCD's L2.
-__device__ __forceinline__ bool gemm_tile(int64_t b, int64_t Mt, int64_t Nt, int64_t& mt, int64_t& nt)
+// Tile and K slice of workgroup (b, z): workgroups b, b + 8, b + 16, ... land on
+// the same XCD, and are given what shares operand rows: the Nt column tiles of
+// one row tile (ceil(Mt / 8) * 8 * Nt x splits workgroups; Mt, Nt: row and
+// column tiles), or by_slice all tiles of one K slice (ceil(splits / 8) * 8 Mt
+// Nt workgroups). The second is for eight slices and more of fewer than eight
+// row tiles, which by rows would leave the other XCDs idle: the 128 x 256 weight
+// gradient over 16,384 rows (two row tiles, 64 slices) takes 12.4 us, 28.4 by
+// rows. Fewer slices of few row tiles stay on one XCD: spread over all, the
+// head's products and their sums took 1 us more (64 pairs 84.3 us a forward
+// pass, 83.3 so).
+__device__ __forceinline__ bool gemm_tile(int32_t by_slice, int64_t b, int64_t splits, int64_t Mt, int64_t Nt,
+                                          int64_t& mt, int64_t& nt, int64_t& z)
 {
+    if (by_slice) {
+        const int64_t tile = b / kXcds % (Mt * Nt);
+        z = b / (kXcds * Mt * Nt) * kXcds + b % kXcds;
+        mt = tile / Nt;
+        nt = tile % Nt;
+        return z < splits;
+    }
     const int64_t grp = b / (kXcds * Nt), r = b % (kXcds * Nt);
     mt = grp * kXcds + r % kXcds;
     nt = r / kXcds;
@@ -116,17 +130,19 @@ __device__ __forceinline__ void gemm_load(const float* __restrict__ A, bool kc, 
 // thread stages the eight K values of one row of each operand in one 16-byte
 // store. The next step's values are loaded while this one is multiplied, into
 // the other of two LDS tiles. Bound by load latency and launch at this model's
-// sizes: the thirteen products of a training step at batch 32 average 9.4 us
+// sizes: the thirteen products of a training step at batch 32 average 8.9 us
 // (36 with a 2-byte store per element and the loads between two barriers).
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
 {
     __shared__ __attribute__((aligned(16))) uint16_t As[2][kGT][kGK + kLdsPad];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kGT][kGK + kLdsPad];
     int64_t mt, nt;
-    if (!gemm_tile(blockIdx.x, (g.M + kGT - 1) / kGT, (g.N + kGT - 1) / kGT, mt, nt)) return;   // whole workgroup
+    int64_t z = blockIdx.z;
+    if (!gemm_tile(g.by_slice, blockIdx.x, g.splits, (g.M + kGT - 1) / kGT, (g.N + kGT - 1) / kGT, mt, nt, z))
+        return;   // whole workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m0 = mt * kGT, n0 = nt * kGT;
-    const int64_t kbeg = (int64_t)blockIdx.z * g.kper;
+    const int64_t kbeg = z * g.kper;
     const int64_t kend = min(g.K, kbeg + g.kper);
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     f32x4_t acc[2][2];
@@ -204,7 +220,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
         }
         return;
     }
-    float* Cz = g.C + (int64_t)blockIdx.z * g.c_split;
+    float* Cz = g.C + z * g.c_split;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll

@@ -91,3 +91,14 @@ def test_gradients_agree_between_layers(P, B):
     assert np.isfinite(grad).all()
     for layers, (gap, size) in euler_gaps(np.asarray(params, np.float64), grad, K).items():
         assert gap <= 2.0 ** -6 * size, layers
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,splits", [(33, 600, 512, 7), (64, 130, 288, 8), (64, 130, 288, 9), (448, 65, 640, 20),
+                                          (449, 65, 640, 20), (128, 256, 4096, 64), (130, 1, 320, 10)])
+def test_products_over_every_map_of_tiles_and_slices(ta, tb, M, N, K, splits):
+    """Seven and eight row tiles, seven to nine slices and counts off eight: integers, so exact."""
+    rng = np.random.default_rng(M + N + K + splits + ta)
+    A, B, bias, C0 = T._gemm_case(ta, tb, M, N, K, rng, integer=True)
+    got = T._run_gemm(A, B, bias, C0, ta, tb, 1, 1, splits)
+    assert np.array_equal(got, T._oracle_gemm(A, B, bias, C0, ta, tb, 1, 1))
