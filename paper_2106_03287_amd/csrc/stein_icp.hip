@@ -475,18 +475,37 @@ int64_t partial_elems(const stein_icp_ctx* c)
     return n;
 }
 
+// Work table and search buffers of the context's shape. The new buffers are
+// allocated before the old ones go, or, where both do not fit, in their place:
+// a failure then leaves none, and the caller either restores the shape before
+// or leaves the context without (need_buffers). The indexed search has no work
+// table.
 int upload_tiling(stein_icp_ctx* c, hipStream_t s)
 {
     build_work(c);
-    if (c->d_work) HIP_TRY(hipFree(c->d_work));
-    if (c->partial) HIP_TRY(hipFree(c->partial));
+    WorkItem* work = nullptr;
+    uint64_t* partial = nullptr;
+    auto alloc = [&] {
+        const size_t bytes = sizeof(WorkItem) * c->work.size();
+        if ((bytes == 0 || hipMalloc(&work, bytes) == hipSuccess) &&
+            hipMalloc(&partial, sizeof(uint64_t) * std::max<int64_t>(partial_elems(c), 1)) == hipSuccess)
+            return true;
+        (void)hipGetLastError();
+        if (work) (void)hipFree(work);
+        work = nullptr;
+        partial = nullptr;
+        return false;
+    };
+    const bool beside = alloc();
+    if (c->d_work) (void)hipFree(c->d_work);
+    if (c->partial) (void)hipFree(c->partial);
     c->d_work = nullptr;
     c->partial = nullptr;
-    if (hipMalloc(&c->d_work, sizeof(WorkItem) * std::max<size_t>(c->work.size(), 1)) != hipSuccess ||
-        hipMalloc(&c->partial, sizeof(uint64_t) * std::max<int64_t>(partial_elems(c), 1)) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(STEIN_ICP_E_NOMEM, "device allocation of the NN work table failed");
-    }
+    for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);   // they hold the old buffers
+    c->graphs.clear();
+    if (!beside && !alloc()) return fail(STEIN_ICP_E_NOMEM, "device allocation of the NN work table failed");
+    c->d_work = work;
+    c->partial = partial;
     HIP_TRY(hipMemcpyAsync(c->d_pairs, c->pairs.data(), sizeof(PairDesc) * c->P, hipMemcpyHostToDevice, s));
     if (!c->indexed) {
         HIP_TRY(hipMemcpyAsync(c->d_groups, c->groups.data(), sizeof(PairDesc) * c->groups.size(),
@@ -495,9 +514,15 @@ int upload_tiling(stein_icp_ctx* c, hipStream_t s)
                                s));
     }
     HIP_TRY(hipStreamSynchronize(s));
-    for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);
-    c->graphs.clear();
     return STEIN_ICP_OK;
+}
+
+// Whether the context can search: not after a change of shape that failed and
+// whose shape before could not be restored.
+int need_buffers(const stein_icp_ctx* c)
+{
+    if (c->partial) return STEIN_ICP_OK;
+    return fail(STEIN_ICP_E_NOMEM, "the context has no search buffers: a change of its search shape ran out of memory");
 }
 
 NNArgs nn_args(const stein_icp_ctx* c)
@@ -1532,6 +1557,8 @@ int stein_icp_step(stein_icp_ctx* ctx, int32_t n_iters, void* hip_stream)
 {
     if (!ctx) return fail(STEIN_ICP_E_INVALID, "ctx is NULL");
     if (n_iters < 0) return fail(STEIN_ICP_E_INVALID, "n_iters must be >= 0");
+    const int rc = need_buffers(ctx);
+    if (rc) return rc;
     return run_iters(ctx, n_iters, (hipStream_t)hip_stream);
 }
 
@@ -1671,9 +1698,12 @@ int stein_icp_set_nn_tiling(stein_icp_ctx* ctx, int32_t qpl, int32_t waves, int3
     ctx->tiling = t;
     ctx->indexed = false;   // the caller asks for a brute-force shape
     const int rc = upload_tiling(ctx, (hipStream_t)hip_stream);
-    if (rc) {
+    if (rc) {   // back to the shape before, its buffers and the pairs' layout in them
+        const std::string why = g_err;
         ctx->tiling = old;
         ctx->indexed = indexed;
+        (void)upload_tiling(ctx, (hipStream_t)hip_stream);
+        return fail(rc, why);
     }
     return rc;
 }
@@ -1682,12 +1712,13 @@ int stein_icp_stage_times(stein_icp_ctx* ctx, int32_t n_iters, double* ms_out, v
 {
     if (!ctx || !ms_out) return fail(STEIN_ICP_E_INVALID, "ctx or ms_out is NULL");
     if (n_iters < 1) return fail(STEIN_ICP_E_INVALID, "n_iters must be >= 1");
+    int rc = need_buffers(ctx);
+    if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(s, &st));
     if (st != hipStreamCaptureStatusNone) return fail(STEIN_ICP_E_STATE, "stream is capturing");
     std::vector<hipEvent_t> ev((size_t)n_iters * (kStages + 1), nullptr);
-    int rc = STEIN_ICP_OK;
     for (auto& e : ev)
         if (hipEventCreate(&e) != hipSuccess) rc = fail(STEIN_ICP_E_DEVICE, "hipEventCreate failed");
     const size_t W = kStages + 1;
@@ -1724,6 +1755,8 @@ int stein_icp_time_nn(stein_icp_ctx* ctx, int32_t n_launches, double* ms_per_lau
 {
     if (!ctx || !ms_per_launch) return fail(STEIN_ICP_E_INVALID, "ctx or ms_per_launch is NULL");
     if (n_launches < 1) return fail(STEIN_ICP_E_INVALID, "n_launches must be >= 1");
+    const int rc = need_buffers(ctx);
+    if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY(hipEventCreate(&e0));

@@ -1,0 +1,117 @@
+"""The library's host code against a stand-in for the HIP runtime
+(fake_hip.cpp): what it launches, allocates and keeps at sizes, limits and
+errors that a GPU test cannot bring about. No kernel runs, and every case is a
+process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = '''
+import ctypes as C
+import sys
+F = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+for f in ("fake_live", "fake_peak", "fake_threads", "fake_arg"):
+    getattr(F, f).restype = C.c_uint64
+F.fake_name.restype = C.c_char_p
+F.fake_limit.argtypes = [C.c_uint64]
+F.fake_is_device.argtypes = [C.c_uint64]
+F.fake_arg.argtypes = F.fake_threads.argtypes = [C.c_int, C.c_int]
+from paper_2106_03287_amd import stein_icp as S
+L = S.lib()
+assert "torch" not in sys.modules
+
+def malloc(n):
+    p = C.c_void_p()
+    assert F.hipMalloc(C.byref(p), C.c_size_t(n)) == 0
+    return p
+
+def init(n_src, n_ref, pairs=1, shared=False, **cfg):
+    """(status, context) of a batch of equal pairs."""
+    cfg.setdefault("use_graph", 0)
+    c = S.stein_icp_default_config(**cfg)
+    src = [malloc(12 * n_src)] * pairs if shared else [malloc(12 * n_src) for _ in range(pairs)]
+    ref = [malloc(12 * n_ref)] * pairs if shared else [malloc(12 * n_ref) for _ in range(pairs)]
+    vp, i64 = C.c_void_p * pairs, C.c_int64 * pairs
+    sched = malloc(4 * c.schedule_rows * c.batch_size)
+    ctx = C.c_void_p()
+    rc = L.stein_icp_batch_init(C.byref(ctx), C.byref(c), pairs, vp(*[s.value for s in src]), i64(*[n_src] * pairs),
+                                vp(*[r.value for r in ref]), i64(*[n_ref] * pairs), None,
+                                vp(*[sched.value] * pairs), None)
+    return rc, ctx
+
+def names():
+    return [F.fake_name(i).decode() for i in range(F.fake_launches())]
+
+def ran(part):
+    return sum(part in n for n in names())
+
+def ok(rc):
+    assert rc == 0, (rc, S.stein_icp_last_error())
+'''
+
+
+@pytest.fixture(scope="session")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"),
+                           "-o", out])
+    return out
+
+
+def run(fake, body, *args):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), fake, *map(str, args)], cwd=ROOT,
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_a_context_launches_its_three_stages(fake):
+    run(fake, """
+        rc, ctx = init(500, 2000, batch_size=100, num_particles=100)
+        ok(rc)
+        F.fake_clear()
+        ok(L.stein_icp_step(ctx, 2, None))
+        assert len(names()) == 6 and ran("index_nn_kernel") == 2, names()
+        L.stein_icp_destroy(ctx)
+    """)
+
+
+def test_a_shape_that_does_not_fit_leaves_the_context_as_it_was(fake):
+    """The search's buffers after a refused change of shape: those of the
+    shape before, and a step launches on them. Where even these cannot be had
+    again, a step is refused and launches nothing, until a shape fits."""
+    run(fake, """
+        for nn_mode in (S.NN_FP32, S.NN_F16_RERANK):
+            rc, ctx = init(500, 2000, batch_size=100, num_particles=100, nn_mode=nn_mode)
+            ok(rc)
+            if nn_mode != S.NN_FP32:   # the screen's fragments are built
+                ok(L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None))
+                ok(L.stein_icp_set_nn_tiling(ctx, 1, 4, 2016, 0, None))
+            F.fake_limit(F.fake_live() + 1000)
+            assert L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None) == S.E_NOMEM
+            F.fake_clear()
+            ok(L.stein_icp_step(ctx, 1, None))
+            if nn_mode == S.NN_FP32:
+                assert "index_nn_kernel" in names()[0] and F.fake_is_device(F.fake_arg(0, 4))
+            else:
+                chunk = C.c_int32()
+                ok(L.stein_icp_nn_tiling(ctx, None, None, C.byref(chunk), None, None, None))
+                assert chunk.value == 2016 and "nn_bf16_kernel" in names()[0]
+            F.fake_limit(1)
+            assert L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None) == S.E_NOMEM
+            F.fake_clear()
+            ms = (C.c_double * 3)()
+            for rc in (L.stein_icp_step(ctx, 1, None), L.stein_icp_stage_times(ctx, 1, ms, None),
+                       L.stein_icp_time_nn(ctx, 1, ms, None)):
+                assert rc == S.E_NOMEM
+            assert not names()
+            F.fake_limit(1 << 62)
+            ok(L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None))
+            ok(L.stein_icp_step(ctx, 1, None))
+            L.stein_icp_destroy(ctx)
+    """)
