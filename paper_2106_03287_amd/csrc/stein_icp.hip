@@ -1223,10 +1223,17 @@ int build_screen(stein_icp_ctx* c, hipStream_t s)
         c->apack = nullptr;
         return fail(STEIN_ICP_E_NOMEM, "device allocation of the screen's fragments failed");
     }
-    HIP_TRY(hipMemcpyAsync(c->d_upairs, uref.data(), sizeof(PairDesc) * uref.size(), hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_pack_bf16(c->d_upairs, (int32_t)uref.size(), maxblk, c->ref4, c->apack,
-                             screen_fmt(c->cfg.nn_mode), s));
-    HIP_TRY(hipStreamSynchronize(s));
+    hipError_t e = hipMemcpyAsync(c->d_upairs, uref.data(), sizeof(PairDesc) * uref.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = launch_pack_bf16(c->d_upairs, (int32_t)uref.size(), maxblk, c->ref4, c->apack,
+                             screen_fmt(c->cfg.nn_mode), s);
+    const hipError_t e2 = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess) {   // fragments that are there are packed ones
+        (void)hipFree(c->apack);
+        c->apack = nullptr;
+        return fail(STEIN_ICP_E_DEVICE, std::string("packing the screen's fragments: ") + hipGetErrorString(e));
+    }
     return STEIN_ICP_OK;
 }
 

@@ -33,7 +33,6 @@ size_t g_live = 0, g_peak = 0, g_limit = SIZE_MAX;
 std::map<const void*, std::string> g_kernels;
 std::vector<Launch> g_log;
 std::map<std::string, int> g_fail;   // calls until the one that fails
-std::map<std::string, int> g_calls;
 uint64_t g_blocks = 0;
 int g_last = kOk;
 int g_device = 0;
@@ -47,7 +46,6 @@ int done(int e)
 
 bool injected(const char* fn)
 {
-    ++g_calls[fn];
     const auto it = g_fail.find(fn);
     if (it == g_fail.end()) return false;
     if (--it->second > 0) return false;
@@ -100,8 +98,8 @@ size_t fake_live() { return g_live; }
 size_t fake_peak() { return g_peak; }
 void fake_peak_reset() { g_peak = g_live; }
 void fake_fail(const char* fn, int nth) { g_fail[fn] = nth; }
-void fake_clear() { g_log.clear(); g_calls.clear(); g_fail.clear(); }
-int fake_calls(const char* fn) { return g_calls[fn]; }
+void fake_no_failures() { g_fail.clear(); g_last = kOk; }
+void fake_clear() { g_log.clear(); fake_no_failures(); }
 int fake_launches() { return (int)g_log.size(); }
 const char* fake_name(int i) { return g_log[i].name; }
 uint64_t fake_threads(int i, int d) { return (uint64_t)g_log[i].grid[d] * g_log[i].block[d]; }

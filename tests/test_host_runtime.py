@@ -115,3 +115,26 @@ def test_a_shape_that_does_not_fit_leaves_the_context_as_it_was(fake):
             ok(L.stein_icp_step(ctx, 1, None))
             L.stein_icp_destroy(ctx)
     """)
+
+
+def test_a_screen_whose_build_failed_is_built_again(fake):
+    """Every copy and launch of a screen's build in turn fails; the next
+    request of a brute-force shape builds the fragments anew."""
+    run(fake, """
+        for what in ("hipMemcpyAsync", "hipLaunchKernel", "hipMalloc"):
+            for nth in range(1, 12):
+                rc, ctx = init(500, 2000, batch_size=100, num_particles=100, nn_mode=S.NN_F16_RERANK)
+                ok(rc)
+                F.fake_clear()
+                F.fake_fail(what.encode(), nth)
+                rc = L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None)
+                F.fake_no_failures()
+                if rc == 0:   # past the last call of the build and the upload
+                    break
+                ok(L.stein_icp_set_nn_tiling(ctx, 1, 4, 32, 0, None))
+                ok(L.stein_icp_step(ctx, 1, None))
+                assert ran("pack_f16_refs") >= 1, (what, nth)
+                assert ran("nn_bf16_kernel") == 1
+                L.stein_icp_destroy(ctx)
+            assert nth < 11
+    """)
