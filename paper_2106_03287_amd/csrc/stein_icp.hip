@@ -142,6 +142,12 @@ int32_t default_chunk(int64_t n_ref_pad, int64_t nq, int q, int64_t pairs)
     return (int32_t)round_up(ceil_div(n_ref_pad, c), 4 * kTile);
 }
 
+// Whether one launch of the indexed search takes nq queries of a pair: the
+// runtime refuses 2^32 threads and more along a grid, and the workgroups beside
+// the search are at most 2^18 threads. (The brute-force searches take one
+// or two a query by default.)
+bool index_launches(int lanes, int64_t nq) { return lanes * nq <= ((int64_t)1 << 32) - ((int64_t)1 << 20); }
+
 // Lanes per query of the indexed search. Few queries leave the chip to a few
 // wavefronts, whose dependent steps bound the launch: with 16 lanes a
 // wavefront waits for the longest of 4 queries, with 4 of 16. Many queries are
@@ -853,6 +859,7 @@ int autotune(stein_icp_ctx* c, hipStream_t s)
     };
     if (c->indexed) {
         for (int lanes : {4, 16}) {
+            if (!index_launches(lanes, c->nq)) continue;
             Tiling t = c->tiling;
             t.lanes = lanes;
             double ms = 0.0;
@@ -1036,6 +1043,7 @@ bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
 {
     double evals = 0.0, queries = 0.0;
     for (const auto& pd : pairs) {
+        if (!index_launches(4, pd.nq)) return false;
         evals += (double)pd.nq * (double)pd.n_ref;
         queries += (double)pd.nq;
     }
@@ -1183,7 +1191,7 @@ int run_indexed_nn(const char* fn, IndexedNn& n, const float* q_xyz, int64_t nq,
 // 202 / 220; 100,000 x 100 225 / 353.
 bool nn_builds_index(int64_t nq, int64_t n_ref, bool host_centre)
 {
-    if (n_ref > kIndexMaxRef) return false;
+    if (n_ref > kIndexMaxRef || !index_launches(4, nq)) return false;
     const double pairs = (double)nq * (double)n_ref;
     if (host_centre) return n_ref <= kChunk || n_ref > 65536 || pairs >= 3e7;
     return n_ref <= kChunk ? n_ref >= 1024 && pairs >= 3e7 : pairs >= 2.5e8;

@@ -138,3 +138,29 @@ def test_a_screen_whose_build_failed_is_built_again(fake):
                 L.stein_icp_destroy(ctx)
             assert nth < 11
     """)
+
+
+def test_searches_too_large_for_an_indexed_launch_take_the_brute_force_one(fake):
+    """A launch takes fewer than 2^32 threads. The indexed search needs 4 or 16
+    a query, the brute-force one one or two by default: contexts and stand-alone
+    searches just below and at the line are launched either way, in every mode."""
+    run(fake, """
+        for nn_mode in (S.NN_FP32, S.NN_BF16_RERANK, S.NN_F16_RERANK):
+            for K, m, autotune, indexed in ((1000, 1 << 20, 0, True), (1024, 1 << 20, 0, False),
+                                            (1024, 1 << 21, 0, False), (256, 1 << 20, 1, True),
+                                            (1000, 1 << 20, 1, True)):
+                rc, ctx = init(m, 100, num_particles=K, batch_size=m, nn_mode=nn_mode, autotune=autotune)
+                ok(rc)
+                F.fake_clear()
+                ok(L.stein_icp_step(ctx, 1, None))
+                assert len(names()) == 3 and ("index_nn" in names()[0]) == indexed, (nn_mode, K, m, names())
+                L.stein_icp_destroy(ctx)
+            ref = malloc(12 * 100000)
+            for nq, indexed in ((1000 << 20, True), (1 << 30, False), ((1 << 31) - 64, False)):
+                q, idx = malloc(12 * nq), malloc(4 * nq)
+                F.fake_clear()
+                ok(L.stein_icp_nn(q, nq, ref, 2000, nn_mode, idx, None, None))
+                assert ran("index_nn") == indexed, (nn_mode, nq, names())
+                assert ran("nn_finish") == 1
+                F.hipFree(q), F.hipFree(idx)
+    """)
