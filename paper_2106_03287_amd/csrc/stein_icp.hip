@@ -214,6 +214,7 @@ struct stein_icp_ctx {
     // nn_mode until stein_icp_set_nn_tiling asks for a brute-force shape
     bool indexed = false;
     int index_levels = 2;           // most levels of a cloud
+    char* index_mem = nullptr;      // what follows, an allocation of its own
     IndexDesc* d_idesc = nullptr;   // one per packed reference
     int32_t* d_cloud = nullptr;     // index of each pair's packed reference
     float4* nodes = nullptr;
@@ -980,16 +981,11 @@ int run_knn(const float4* q4, int64_t nq, const float4* ref4, int64_t n_ref, int
     return STEIN_ICP_OK;
 }
 
-// Normals of an indexed cloud's references (nrm: 4 doubles per reference).
-// Scratch is allocated here and freed after the stream has drained.
-int run_index_normals(const IndexDesc& d, const IndexDesc* d_desc, const float4* nodes, const float4* ref4, int32_t k,
-                      double* nrm, hipStream_t s)
+// Normals of an indexed cloud's references (nrm: 4 doubles per reference), on
+// the stream. lists: scratch of 8 d.n k bytes.
+hipError_t enqueue_index_normals(const IndexDesc& d, const IndexDesc* d_desc, const float4* nodes, const float4* ref4,
+                                 int32_t k, uint64_t* lists, double* nrm, hipStream_t s)
 {
-    uint64_t* lists = nullptr;
-    if (hipMalloc(&lists, 8 * (size_t)d.n * (size_t)k) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(STEIN_ICP_E_NOMEM, "device allocation for the neighbour lists failed");
-    }
     IndexKnnArgs a{};
     a.desc = d_desc;
     a.nodes = nodes;
@@ -1012,12 +1008,7 @@ int run_index_normals(const IndexDesc& d, const IndexDesc* d_desc, const float4*
         hipLaunchKernelGGL(index_knn_kernel<2>, grid, block, lds, s, a);
         hipLaunchKernelGGL(knn_merge_kernel<kKnnMax>, grid1d(d.n, 64), dim3(64), 0, s, b);
     }
-    hipError_t e = hipGetLastError();
-    const hipError_t e2 = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = e2;
-    (void)hipFree(lists);
-    if (e != hipSuccess) return fail(STEIN_ICP_E_DEVICE, std::string("normals: ") + hipGetErrorString(e));
-    return STEIN_ICP_OK;
+    return hipGetLastError();
 }
 
 void free_ctx(stein_icp_ctx* c)
@@ -1030,7 +1021,18 @@ void free_ctx(stein_icp_ctx* c)
     if (c->d_work) (void)hipFree(c->d_work);
     if (c->partial) (void)hipFree(c->partial);
     if (c->apack) (void)hipFree(c->apack);
+    if (c->index_mem) (void)hipFree(c->index_mem);
     delete c;
+}
+
+// Back to the brute-force search of the context's mode, whose fragments (of a
+// screen) are the caller's to build.
+void drop_index(stein_icp_ctx* c)
+{
+    (void)hipGetLastError();
+    if (c->index_mem) (void)hipFree(c->index_mem);
+    c->index_mem = nullptr;
+    c->indexed = false;
 }
 
 // Whether a context's searches repay an index. Below 1.5e7 pair evaluations an
@@ -1052,13 +1054,14 @@ bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
 
 // Device memory of an index build besides the nodes and the plan.
 struct IndexScratch {
-    size_t plan = 0, split = 0, state = 0, hist = 0;   // bytes
+    size_t plan = 0, split = 0, state = 0, hist = 0;   // bytes, multiples of 256
     explicit IndexScratch(const IndexPlan& pl)
     {
-        plan = sizeof(IndexDesc) * pl.desc.size() + sizeof(IndexSeg) * pl.seg.size() +
-               sizeof(IndexTile) * (pl.tile.size() + pl.top_tile.size()) + sizeof(IndexChunk) * pl.chunk.size();
-        split = 2 * sizeof(float4) * (size_t)pl.points;
-        state = sizeof(IndexSegState) * pl.seg.size();
+        const auto up = [](size_t n) { return (size_t)round_up((int64_t)n, 256); };
+        plan = up(sizeof(IndexDesc) * pl.desc.size() + sizeof(IndexSeg) * pl.seg.size() +
+                  sizeof(IndexTile) * (pl.tile.size() + pl.top_tile.size()) + sizeof(IndexChunk) * pl.chunk.size());
+        split = up(2 * sizeof(float4) * (size_t)pl.points);
+        state = up(sizeof(IndexSegState) * pl.seg.size());
         hist = 4 * (size_t)kSplitBins * pl.seg.size();
     }
 };
@@ -1337,7 +1340,6 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         if (!c->indexed) plan = IndexPlan();
         for (const auto& d : plan.desc) c->index_levels = std::max(c->index_levels, (int)d.levels);
     }
-    const IndexScratch scr(plan);
     const int64_t PK6 = (int64_t)P * K * 6;
     const int64_t npairs2 = K >= 2 ? (int64_t)K * (K - 1) : 1;
     size_t off = 0;
@@ -1358,9 +1360,6 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     const size_t o_step = take(8 * (size_t)P), o_stepn = take(8 * (size_t)P);
     const size_t o_pose = take(sizeof(Pose) * (size_t)P * K);
     const size_t o_queries = take(sizeof(float4) * (size_t)P * nq);
-    const size_t o_nodes = take(sizeof(float4) * (size_t)plan.nodes), o_split = take(scr.split);
-    const size_t o_plan = take(scr.plan), o_state = take(scr.state), o_hist = take(scr.hist);
-    const size_t o_cloud = take(4 * (size_t)P);
     const size_t o_match = take(4 * (size_t)P * nq);
     const bool plane = cfg->metric == STEIN_ICP_METRIC_PLANE;
     const size_t o_nrm = take(plane ? 32 * (size_t)ro : 32);
@@ -1389,9 +1388,6 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     c->parity = 0;
     c->pose = (Pose*)(c->arena + o_pose);
     c->queries = (float4*)(c->arena + o_queries);
-    c->nodes = (float4*)(c->arena + o_nodes);
-    c->d_idesc = (IndexDesc*)(c->arena + o_plan);
-    c->d_cloud = (int32_t*)(c->arena + o_cloud);
     c->d_upairs = (PairDesc*)(c->arena + o_upairs);
     c->match = (int32_t*)(c->arena + o_match);
     c->nrm = (double*)(c->arena + o_nrm);
@@ -1403,6 +1399,34 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         free_ctx(c);
         return code;
     };
+    // The index has an allocation of its own beside the arena, and its build (and
+    // the neighbour lists of the normals, in the same place afterwards) one that
+    // goes before the search's buffers come. A context that has no room for them
+    // searches without.
+    struct Scratch {
+        char* p = nullptr;
+        void release()
+        {
+            if (p) (void)hipFree(p);
+            p = nullptr;
+        }
+        ~Scratch() { release(); }
+    } build;
+    const IndexScratch scr(plan);
+    if (c->indexed) {
+        const size_t nodes = sizeof(float4) * (size_t)plan.nodes;
+        size_t lists = 0;
+        if (plane)
+            for (const auto& pd : uref) lists = std::max(lists, 8 * (size_t)pd.n_ref * (size_t)cfg->normal_k);
+        if (hipMalloc(&c->index_mem, nodes + scr.plan + 4 * (size_t)P) == hipSuccess &&
+            hipMalloc(&build.p, std::max(lists, scr.state + scr.hist + scr.split) + 256) == hipSuccess) {
+            c->nodes = (float4*)c->index_mem;
+            c->d_idesc = (IndexDesc*)(c->index_mem + nodes);
+            c->d_cloud = (int32_t*)(c->index_mem + nodes + scr.plan);
+        } else {
+            drop_index(c);
+        }
+    }
     if (hipMemsetAsync(c->arena, 0, off, s) != hipSuccess) return bail(fail(STEIN_ICP_E_DEVICE, "hipMemsetAsync failed"));
 
     std::vector<int32_t> hsched;
@@ -1465,12 +1489,13 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         IndexBuildArgs b{};
         b.ref4 = c->ref4;
         b.nodes = c->nodes;
-        b.split[0] = (float4*)(c->arena + o_split);
+        b.state = (IndexSegState*)build.p;
+        b.hist = (uint32_t*)(build.p + scr.state);
+        b.split[0] = (float4*)(build.p + scr.state + scr.hist);
         b.split[1] = b.split[0] + plan.points;
-        b.state = (IndexSegState*)(c->arena + o_state);
-        b.hist = (uint32_t*)(c->arena + o_hist);
-        if (hipMemcpyAsync(c->d_cloud, cloud.data(), 4 * (size_t)P, hipMemcpyHostToDevice, s) != hipSuccess ||
-            enqueue_index_build(plan, blob, c->arena + o_plan, b, s) != hipSuccess)
+        if (hipMemsetAsync(build.p, 0, scr.state + scr.hist, s) != hipSuccess ||
+            hipMemcpyAsync(c->d_cloud, cloud.data(), 4 * (size_t)P, hipMemcpyHostToDevice, s) != hipSuccess ||
+            enqueue_index_build(plan, blob, (char*)c->d_idesc, b, s) != hipSuccess)
             return bail(fail(STEIN_ICP_E_DEVICE, "index build launch failed"));
     }
     int flag = 0;
@@ -1483,10 +1508,13 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
     if (plane) {
         for (size_t u = 0; u < uref.size(); ++u) {
             const PairDesc& pd = uref[u];
-            rc = c->indexed ? run_index_normals(plan.desc[u], c->d_idesc + u, c->nodes, c->ref4 + pd.ref_off,
-                                                cfg->normal_k, c->nrm + 4 * pd.ref_off, s)
-                            : run_knn(c->ref4 + pd.ref_off, pd.n_ref, c->ref4 + pd.ref_off, pd.n_ref, cfg->normal_k, nullptr,
-                         nullptr, c->nrm + 4 * pd.ref_off, 4, nullptr, s);
+            const float4* r = c->ref4 + pd.ref_off;
+            double* nrm = c->nrm + 4 * pd.ref_off;
+            if (!c->indexed)
+                rc = run_knn(r, pd.n_ref, r, pd.n_ref, cfg->normal_k, nullptr, nullptr, nrm, 4, nullptr, s);
+            else if (enqueue_index_normals(plan.desc[u], c->d_idesc + u, c->nodes, r, cfg->normal_k, (uint64_t*)build.p,
+                                           nrm, s) != hipSuccess)
+                rc = fail(STEIN_ICP_E_DEVICE, "normals launch failed");
             if (rc) return bail(rc);
         }
     }
@@ -1494,7 +1522,15 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         rc = build_screen(c, s);
         if (rc) return bail(rc);
     }
+    if (build.p && hipStreamSynchronize(s) != hipSuccess)
+        return bail(fail(STEIN_ICP_E_DEVICE, "init synchronisation failed"));
+    build.release();
     rc = upload_tiling(c, s);
+    if (rc == STEIN_ICP_E_NOMEM && c->indexed) {   // the keys' room is the index's
+        drop_index(c);
+        rc = is_screen(cfg->nn_mode) ? build_screen(c, s) : STEIN_ICP_OK;
+        if (!rc) rc = upload_tiling(c, s);
+    }
     if (rc) return bail(rc);
     if (cfg->autotune) {
         rc = autotune(c, s);

@@ -32,7 +32,10 @@ std::map<char*, size_t> g_mem;
 size_t g_live = 0, g_peak = 0, g_limit = SIZE_MAX;
 std::map<const void*, std::string> g_kernels;
 std::vector<Launch> g_log;
-std::map<std::string, int> g_fail;   // calls until the one that fails
+struct Failure {
+    int in, times;   // calls until the first that fails, and how many do
+};
+std::map<std::string, Failure> g_fail;
 uint64_t g_blocks = 0;
 int g_last = kOk;
 int g_device = 0;
@@ -48,8 +51,9 @@ bool injected(const char* fn)
 {
     const auto it = g_fail.find(fn);
     if (it == g_fail.end()) return false;
-    if (--it->second > 0) return false;
-    g_fail.erase(it);
+    Failure& f = it->second;
+    if (--f.in > 0) return false;
+    if (--f.times == 0) g_fail.erase(it);
     return true;
 }
 
@@ -97,7 +101,7 @@ void fake_limit(size_t bytes) { g_limit = bytes; }
 size_t fake_live() { return g_live; }
 size_t fake_peak() { return g_peak; }
 void fake_peak_reset() { g_peak = g_live; }
-void fake_fail(const char* fn, int nth) { g_fail[fn] = nth; }
+void fake_fail(const char* fn, int nth, int times) { g_fail[fn] = Failure{nth, times}; }
 void fake_no_failures() { g_fail.clear(); g_last = kOk; }
 void fake_clear() { g_log.clear(); fake_no_failures(); }
 int fake_launches() { return (int)g_log.size(); }
