@@ -11,6 +11,7 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "stein_icp.h"
@@ -164,19 +165,12 @@ Tiling default_tiling(const std::vector<PairDesc>& pd, int64_t nq)
     return t;
 }
 
-// Tuned shapes by (pairs, queries per pair, total padded references),
-// shared by every context of the process.
-struct TuneKey {
-    int32_t P;
-    int64_t nq, refs;
-    bool indexed;
-    bool operator<(const TuneKey& o) const
-    {
-        if (P != o.P) return P < o.P;
-        if (nq != o.nq) return nq < o.nq;
-        return refs != o.refs ? refs < o.refs : indexed < o.indexed;
-    }
-};
+// Tuned shapes, shared by every context of the process, by what decides the
+// candidates and their times: pairs, queries per pair, total padded
+// references, whether the search is indexed, the mode of one that is not (the
+// screens are built for fewer shapes than the FP32 search), particles (whether
+// the bandwidths are selected beside the search), constant bandwidths, metric.
+using TuneKey = std::tuple<int32_t, int64_t, int64_t, bool, int32_t, int32_t, bool, int32_t>;
 std::map<TuneKey, std::pair<Tiling, double>> g_tuned;
 
 }  // namespace
@@ -821,12 +815,13 @@ int run_iters(stein_icp_ctx* c, int32_t n, hipStream_t s)
 // parallelism against the gradient kernel's reduction over chunks) and keep
 // the fastest. Shapes change only the work decomposition, never the
 // arithmetic, so results are identical for every candidate. Results are
-// cached per (pairs, queries, references) for the process.
+// cached for the process (TuneKey).
 int autotune(stein_icp_ctx* c, hipStream_t s)
 {
     int64_t refs = 0;
     for (const auto& pd : c->pairs) refs += pd.n_ref_pad;
-    const TuneKey tk{c->P, c->nq, refs, c->indexed};
+    const TuneKey tk{c->P, c->nq, refs, c->indexed, c->indexed ? 0 : c->cfg.nn_mode,
+                     c->K, const_bandwidth(c->cfg), c->cfg.metric};
     auto hit = g_tuned.find(tk);
     if (hit != g_tuned.end()) {
         c->tiling = hit->second.first;

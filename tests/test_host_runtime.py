@@ -213,3 +213,35 @@ def test_an_index_keeps_no_scratch_and_yields_its_room(fake):
                 L.stein_icp_destroy(ctx)
             F.fake_limit(1 << 62)
     """)
+
+
+def test_tuned_shapes_are_shared_by_contexts_alike_only(fake):
+    """A tuned shape goes to the next context of the same sizes, mode, particles
+    and metric, and to no other: a screen cannot take the FP32 search's four
+    queries per lane, and where the bandwidths are selected depends on the
+    particles and the lanes of an indexed search."""
+    run(fake, """
+        def tuned(n_src, n_ref, **cfg):
+            F.fake_clear()
+            rc, ctx = init(n_src, n_ref, autotune=1, **cfg)
+            ok(rc)
+            nn = ran("nn_fp32") + ran("nn_bf16") + ran("index_nn")
+            q = C.c_int32()
+            ok(L.stein_icp_nn_tiling(ctx, C.byref(q), None, None, None, None, None))
+            ok(L.stein_icp_step(ctx, 1, None))
+            L.stein_icp_destroy(ctx)
+            return nn, q.value
+
+        small = dict(n_src=500, n_ref=900, batch_size=100, num_particles=10)   # searched by brute force
+        assert tuned(**small, nn_mode=S.NN_FP32)[1] == 4   # the fewest workgroups, which the stand-in takes for time
+        for mode in (S.NN_BF16_RERANK, S.NN_F16_RERANK):
+            n, q = tuned(**small, nn_mode=mode)
+            assert n > 0 and q <= 2, (mode, n, q)
+        assert tuned(**small, nn_mode=S.NN_FP32) == (0, 4)
+        big = dict(n_src=500, n_ref=20000)
+        for other in (dict(num_particles=100, batch_size=300), dict(num_particles=300, batch_size=100),
+                      dict(num_particles=100, batch_size=300, metric=S.METRIC_PLANE),
+                      dict(num_particles=100, batch_size=300, bandwidth_mode=S.BW_FIXED)):
+            assert tuned(**big, **other)[0] > 0, other
+            assert tuned(**big, **other)[0] == 0, other
+    """)
