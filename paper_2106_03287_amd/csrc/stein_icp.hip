@@ -587,7 +587,8 @@ void launch_index_nn(int lanes, bool bw, int levels, int64_t nq, int64_t pairs, 
 // particles and diagnostics read back: 64 us with copies, 59 so). What
 // only a copy engine may write keeps the copies: memory that is not this
 // device's own, addresses off 4 bytes, overlapping arrays (then the last
-// wins), and larger ones, where the copies' wide loads count.
+// wins), and larger ones, where the copies' wide loads count; and an array past
+// the end of its allocation, which a copy refuses.
 struct OutArray {
     void* dst;
     const void* src;
@@ -613,8 +614,14 @@ hipError_t copy_out(const stein_icp_ctx* c, std::initializer_list<OutArray> arra
             (void)hipGetLastError();   // an address of the host's own
             one = false;
         }
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (one && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)a[i].dst) != hipSuccess) {
+            (void)hipGetLastError();
+            one = false;
+        }
         one = one && (uintptr_t)a[i].dst % 4 == 0 && at.type == hipMemoryTypeDevice && at.device == c->device &&
-              !at.isManaged;
+              !at.isManaged && (char*)a[i].dst + a[i].bytes <= (char*)base + size;
         for (int j = 0; j < i && one; ++j)
             one = (char*)a[i].dst >= (char*)a[j].dst + a[j].bytes || (char*)a[j].dst >= (char*)a[i].dst + a[i].bytes;
     }

@@ -245,3 +245,23 @@ def test_tuned_shapes_are_shared_by_contexts_alike_only(fake):
             assert tuned(**big, **other)[0] > 0, other
             assert tuned(**big, **other)[0] == 0, other
     """)
+
+
+def test_outputs_past_their_allocation_are_refused(fake):
+    """Several outputs in one kernel launch, as long as each lies inside its
+    allocation: one that does not is left to a copy, which refuses it, and no
+    kernel writes past it."""
+    run(fake, """
+        rc, ctx = init(500, 2000, batch_size=100, num_particles=100)
+        ok(rc)
+        n = 8 * 100 * 6
+        whole, short = malloc(n), malloc(n - 8)
+        for a, b, code in ((whole, malloc(n), 0), (whole, short, S.E_DEVICE), (short, whole, S.E_DEVICE),
+                           (C.c_void_p(whole.value + 8), malloc(n), S.E_DEVICE)):
+            F.fake_clear()
+            assert L.stein_icp_get_diagnostics(ctx, a, b, None, None, None) == code
+            assert ran("copy_out") == (code == 0)
+            F.fake_clear()
+            assert L.stein_icp_get_state(ctx, a, b, None, None, None) == code
+            assert ran("copy_out") == (code == 0)
+    """)
