@@ -586,9 +586,10 @@ void launch_index_nn(int lanes, bool bw, int levels, int64_t nq, int64_t pairs, 
 // four where together they are at most 1 MB (a step of 10 particles with its
 // particles and diagnostics read back: 64 us with copies, 59 so). What
 // only a copy engine may write keeps the copies: memory that is not this
-// device's own, addresses off 4 bytes, overlapping arrays (then the last
-// wins), and larger ones, where the copies' wide loads count; and an array past
-// the end of its allocation, which a copy refuses.
+// device's own, a stream of another device (where the kernel would run),
+// addresses off 4 bytes, overlapping arrays (then the last wins), and larger
+// ones, where the copies' wide loads count; and an array past the end of its
+// allocation, which a copy refuses.
 struct OutArray {
     void* dst;
     const void* src;
@@ -606,8 +607,12 @@ hipError_t copy_out(const stein_icp_ctx* c, std::initializer_list<OutArray> arra
             total += o.bytes;
         }
     if (n == 0) return hipSuccess;
-    int dev = -1;
+    int dev = -1, sdev = -1;
     bool one = n > 1 && total <= ((size_t)1 << 20) && hipGetDevice(&dev) == hipSuccess && dev == c->device;
+    if (one && s && (hipStreamGetDevice(s, &sdev) != hipSuccess || sdev != c->device)) {
+        (void)hipGetLastError();
+        one = false;
+    }
     for (int i = 0; i < n && one; ++i) {
         hipPointerAttribute_t at{};
         if (hipPointerGetAttributes(&at, a[i].dst) != hipSuccess) {

@@ -265,3 +265,20 @@ def test_outputs_past_their_allocation_are_refused(fake):
             assert L.stein_icp_get_state(ctx, a, b, None, None, None) == code
             assert ran("copy_out") == (code == 0)
     """)
+
+
+def test_outputs_on_another_devices_stream_are_copied(fake):
+    """A copy on a stream of another device than the context's reads and writes
+    where it is told; a kernel would run on that other device."""
+    run(fake, """
+        rc, ctx = init(500, 2000, batch_size=100, num_particles=100)
+        ok(rc)
+        n = 8 * 100 * 6
+        a, b = malloc(n), malloc(n)
+        for device in (0, 1):
+            s = malloc(8)
+            F.fake_stream_device(s, device)
+            F.fake_clear()
+            ok(L.stein_icp_get_diagnostics(ctx, a, b, None, None, s))
+            assert ran("copy_out") == (device == 0)
+    """)
