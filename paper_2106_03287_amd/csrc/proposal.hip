@@ -306,7 +306,8 @@ int backward(Model* m, hipStream_t s, const float* X, int64_t B)
                     {m->dA1, rows, kF1, g + L.b1}});
 }
 
-// `parts` workgroups a sample; part: B x parts doubles (loss itself for one).
+// `parts` workgroups a sample; part: B x parts doubles, for one part the losses
+// themselves.
 int launch_mmd(hipStream_t s, const float* Xf, const double* Xd, const double* Y, int64_t B, int32_t K,
                const MmdScales& sc, double gscale, float* dX, int32_t parts, double* part, double* loss)
 {
@@ -315,7 +316,7 @@ int launch_mmd(hipStream_t s, const float* Xf, const double* Xd, const double* Y
     if (lds > 65536)
         HIP_TRY(hipFuncSetAttribute((const void*)mmd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     mmd_kernel<<<dim3((unsigned)B, (unsigned)parts), 256, lds, s>>>(Xf, Xd, Y, K, sc, gscale, dX, part);
-    mmd_loss_kernel<<<(unsigned)ceil_div(B, 256), 256, 0, s>>>(part, B, parts, K, loss);
+    if (parts > 1) mmd_loss_kernel<<<(unsigned)ceil_div(B, 256), 256, 0, s>>>(part, B, parts, K, loss);
     HIP_TRY(hipGetLastError());
     return STEIN_ICP_OK;
 }

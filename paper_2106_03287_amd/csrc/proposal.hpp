@@ -722,7 +722,8 @@ __device__ __forceinline__ double mmd_k(const MmdScales& sc, const double* u, co
 // Workgroup (b, r) takes the rows i of part r of gridDim.y, 256 at a time (G =
 // max(1, 256 / rows) threads to a row, each with a range of j; their sums are
 // added in order), and writes its share of the loss to
-// part[b gridDim.y + r]; mmd_loss_kernel adds the shares. Bound by the FP64
+// part[b gridDim.y + r]; mmd_loss_kernel adds the shares (a sample's only
+// workgroup writes the loss itself). Bound by the FP64
 // exponentials: 32 samples of 100 particles took 115 us with one workgroup a
 // sample, which leaves most of the chip idle, 20 with kMmdParts.
 constexpr int kMmdParts = 16;
@@ -760,8 +761,9 @@ __global__ __launch_bounds__(256) void mmd_kernel(const float* __restrict__ Xf, 
                 for (int c = 0; c < 6; ++c) g[c] -= du[c];
                 sum += kxx + mmd_k(sc, y + 6 * i, y + 6 * j, nullptr) - 2.0 * kxy;
             }
+            if (dX)
 #pragma unroll
-            for (int c = 0; c < 6; ++c) gp[t * 6 + c] = g[c];
+                for (int c = 0; c < 6; ++c) gp[t * 6 + c] = g[c];
         }
         __syncthreads();
         if (dX)
@@ -778,7 +780,7 @@ __global__ __launch_bounds__(256) void mmd_kernel(const float* __restrict__ Xf, 
         if (t < s) red[t] += red[t + s];
         __syncthreads();
     }
-    if (t == 0) part[b * gridDim.y + blockIdx.y] = red[0];
+    if (t == 0) part[b * gridDim.y + blockIdx.y] = gridDim.y == 1 ? red[0] / ((double)K * K) : red[0];
 }
 
 // loss[b] = (sum of its shares, in order) / K^2.

@@ -282,3 +282,16 @@ def test_outputs_on_another_devices_stream_are_copied(fake):
             ok(L.stein_icp_get_diagnostics(ctx, a, b, None, None, s))
             assert ran("copy_out") == (device == 0)
     """)
+
+
+def test_the_stand_alone_set_loss_is_one_launch(fake):
+    """One workgroup a sample writes the sample's loss: nothing is left for a
+    second launch, which would read the losses where it writes them."""
+    run(fake, """
+        B, K = 3, 100
+        x, y, out = malloc(48 * B * K), malloc(48 * B * K), malloc(8 * B)
+        sigma = (C.c_double * 6)(*[0.1] * 6)
+        F.fake_clear()
+        ok(L.stein_icp_proposal_mmd(x, y, B, K, 1, sigma, out, None))
+        assert len(names()) == 1, names()
+    """)
