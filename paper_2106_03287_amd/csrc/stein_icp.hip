@@ -1059,6 +1059,9 @@ bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
     return evals >= 1.5e7 || (is_screen(c.nn_mode) && queries > 1024.0);
 }
 
+// A context's index keeps build scratch of at most so much.
+constexpr size_t kKeptScratch = (size_t)8 << 20;
+
 // Device memory of an index build besides the nodes and the plan.
 struct IndexScratch {
     size_t plan = 0, split = 0, state = 0, hist = 0;   // bytes, multiples of 256
@@ -1406,9 +1409,12 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         free_ctx(c);
         return code;
     };
-    // The index has an allocation of its own beside the arena, and its build (and
-    // the neighbour lists of the normals, in the same place afterwards) one that
-    // goes before the search's buffers come. A context that has no room for them
+    // The index has an allocation of its own beside the arena. The scratch of its
+    // build (and the neighbour lists of the normals, in the same place afterwards)
+    // goes before the search's buffers come, unless it is small: then it stays
+    // behind the index, as every allocation of some MB that goes here costs the
+    // next ones a new mapping (a pair of 100,000 references: 267 us of init and 373
+    // of its first graph, 209 and 113 so). A context that has no room for them
     // searches without.
     struct Scratch {
         char* p = nullptr;
@@ -1419,17 +1425,22 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         }
         ~Scratch() { release(); }
     } build;
+    char* scratch = nullptr;
     const IndexScratch scr(plan);
     if (c->indexed) {
         const size_t nodes = sizeof(float4) * (size_t)plan.nodes;
         size_t lists = 0;
         if (plane)
             for (const auto& pd : uref) lists = std::max(lists, 8 * (size_t)pd.n_ref * (size_t)cfg->normal_k);
-        if (hipMalloc(&c->index_mem, nodes + scr.plan + 4 * (size_t)P) == hipSuccess &&
-            hipMalloc(&build.p, std::max(lists, scr.state + scr.hist + scr.split) + 256) == hipSuccess) {
+        const size_t kept = (size_t)round_up((int64_t)(nodes + scr.plan + 4 * (size_t)P), 256);
+        const size_t used = std::max(lists, scr.state + scr.hist + scr.split);
+        const bool small = used <= kKeptScratch;
+        if (hipMalloc(&c->index_mem, kept + (small ? used : 0)) == hipSuccess &&
+            (small || hipMalloc(&build.p, used) == hipSuccess)) {
             c->nodes = (float4*)c->index_mem;
             c->d_idesc = (IndexDesc*)(c->index_mem + nodes);
             c->d_cloud = (int32_t*)(c->index_mem + nodes + scr.plan);
+            scratch = small ? c->index_mem + kept : build.p;
         } else {
             drop_index(c);
         }
@@ -1496,11 +1507,11 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
         IndexBuildArgs b{};
         b.ref4 = c->ref4;
         b.nodes = c->nodes;
-        b.state = (IndexSegState*)build.p;
-        b.hist = (uint32_t*)(build.p + scr.state);
-        b.split[0] = (float4*)(build.p + scr.state + scr.hist);
+        b.state = (IndexSegState*)scratch;
+        b.hist = (uint32_t*)(scratch + scr.state);
+        b.split[0] = (float4*)(scratch + scr.state + scr.hist);
         b.split[1] = b.split[0] + plan.points;
-        if (hipMemsetAsync(build.p, 0, scr.state + scr.hist, s) != hipSuccess ||
+        if ((scr.state && hipMemsetAsync(scratch, 0, scr.state + scr.hist, s) != hipSuccess) ||
             hipMemcpyAsync(c->d_cloud, cloud.data(), 4 * (size_t)P, hipMemcpyHostToDevice, s) != hipSuccess ||
             enqueue_index_build(plan, blob, (char*)c->d_idesc, b, s) != hipSuccess)
             return bail(fail(STEIN_ICP_E_DEVICE, "index build launch failed"));
@@ -1519,7 +1530,7 @@ int init_impl(stein_icp_ctx** out, const stein_icp_config* cfg, int32_t P, const
             double* nrm = c->nrm + 4 * pd.ref_off;
             if (!c->indexed)
                 rc = run_knn(r, pd.n_ref, r, pd.n_ref, cfg->normal_k, nullptr, nullptr, nrm, 4, nullptr, s);
-            else if (enqueue_index_normals(plan.desc[u], c->d_idesc + u, c->nodes, r, cfg->normal_k, (uint64_t*)build.p,
+            else if (enqueue_index_normals(plan.desc[u], c->d_idesc + u, c->nodes, r, cfg->normal_k, (uint64_t*)scratch,
                                            nrm, s) != hipSuccess)
                 rc = fail(STEIN_ICP_E_DEVICE, "normals launch failed");
             if (rc) return bail(rc);

@@ -172,13 +172,13 @@ def test_searches_too_large_for_an_indexed_launch_take_the_brute_force_one(fake)
 
 def test_an_index_keeps_no_scratch_and_yields_its_room(fake):
     """What an indexed context keeps: the packed references (16 bytes each) and
-    the index, whose build scratch goes when init ends. And where the index, its
-    scratch or what follows it does not fit, the context searches without, in no
-    more memory than it needs then."""
+    the index; its build scratch, of clouds of some size, goes when init ends. And
+    where the index, its scratch or what follows it does not fit, the context
+    searches without, in no more memory than it needs then."""
     run(fake, """
         for metric in (S.METRIC_POINT, S.METRIC_PLANE):
             kept = []
-            for n_ref in (100000, 200000):
+            for n_ref in (500000, 1000000):
                 F.fake_limit(1 << 62)
                 cfg = dict(batch_size=300, num_particles=100, metric=metric)
                 rc, ctx = init(500, n_ref, **cfg)
@@ -187,7 +187,7 @@ def test_an_index_keeps_no_scratch_and_yields_its_room(fake):
                 before = F.fake_live()
                 L.stein_icp_destroy(ctx)
                 kept[-1] -= F.fake_live() - 12 * n_ref
-            per_ref = (kept[1] - kept[0]) / 100000
+            per_ref = (kept[1] - kept[0]) / 500000
             assert per_ref < 40 + (32 if metric == S.METRIC_PLANE else 0), per_ref
 
         for nn_mode in (S.NN_FP32, S.NN_F16_RERANK):
@@ -198,7 +198,7 @@ def test_an_index_keeps_no_scratch_and_yields_its_room(fake):
                 F.fake_fail(b"hipMalloc", nth + 3, times)   # after the three inputs
                 live = F.fake_live()
                 F.fake_peak_reset()
-                rc, ctx = init(500, 100000, **cfg)
+                rc, ctx = init(500, 500000, **cfg)
                 F.fake_no_failures()
                 ok(rc)
                 need = F.fake_peak() - live if need is None else need
@@ -206,9 +206,9 @@ def test_an_index_keeps_no_scratch_and_yields_its_room(fake):
                 ok(L.stein_icp_step(ctx, 1, None))
                 assert len(names()) == 3 and not ran("index_nn"), names()
                 L.stein_icp_destroy(ctx)
-            for more in range(0, 8 << 20, 1 << 17):
+            for more in range(0, 40 << 20, 1 << 19):
                 F.fake_limit(F.fake_live() + need + more)
-                rc, ctx = init(500, 100000, **cfg)
+                rc, ctx = init(500, 500000, **cfg)
                 ok(rc)
                 L.stein_icp_destroy(ctx)
             F.fake_limit(1 << 62)
