@@ -1042,12 +1042,22 @@ void drop_index(stein_icp_ctx* c)
     c->indexed = false;
 }
 
-// Whether a context's searches repay an index. Below 1.5e7 pair evaluations an
-// iteration the FP32 brute-force search is as fast or faster (us an
-// iteration, brute force / index: 512 queries x 4,000 19.4 / 23.7, x 20,000
-// 24.9 / 28.0; 10,000 x 1,000 25.4 / 25.6; 5,000 x 4,000 30.0 / 25.1); the
-// screens are only with few queries (512 x 4,000 22.2 / 23.7; 1,600 x 300
-// 25.9 / 22.3).
+// Whether a context's searches repay an index, whose build adds about 30 us to
+// an init (80 where the cloud is cut into chunks; the screens, which then need
+// no fragments, save as much). From 1.5e7 pair evaluations an iteration on it
+// does, but not in FP32 with fewer than 4,096 queries: their chains of dependent
+// steps take longer than so many distances on the whole chip. Brute force /
+// index, us: an iteration of a kept street context, the first five, FP32: 512
+// queries x 15,000 21.4 / 25.2, x 30,000 26.3 / 27.7, x 60,000 40.0 / 30.0;
+// 2,048 x 5,000 21.0 / 23.2, x 15,000 31.1 / 25.2; 5,000 x 5,000 31.0 / 24.9;
+// 10,000 x 5,000 34.1 / 28.0. A pair with its init and 5 (50) iterations, FP32:
+// 2,048 x 7,400 371 / 438 (1,625 / 1,582), x 15,000 409 / 443 (1,972 / 1,659);
+// 5,000 x 1,000 371 / 398 (1,546 / 1,561), x 3,000 402 / 407 (1,817 / 1,564);
+// 10,000 x 1,500 377 / 416 (1,605 / 1,584). The screens, kinect: 1,000 x 4,000
+// 336 / 336 (1,347 / 1,309), x 10,000 362 / 388 (1,441 / 1,488), 512 x 30,000
+// 434 / 408 (1,731 / 1,607), 2,048 x 2,000 399 / 387 (1,691 / 1,443). Normals
+// want every reference's neighbours (33 us from the index for 20,000, 328
+// without), so point-to-plane keeps the lower line.
 bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
 {
     double evals = 0.0, queries = 0.0;
@@ -1056,7 +1066,8 @@ bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
         evals += (double)pd.nq * (double)pd.n_ref;
         queries += (double)pd.nq;
     }
-    return evals >= 1.5e7 || (is_screen(c.nn_mode) && queries > 1024.0);
+    if (is_screen(c.nn_mode)) return evals >= 1.5e7 || queries > 1024.0;
+    return evals >= (queries >= 4096.0 || c.metric == STEIN_ICP_METRIC_PLANE ? 1.5e7 : 3e7);
 }
 
 // A context's index keeps build scratch of at most so much.

@@ -295,3 +295,27 @@ def test_the_stand_alone_set_loss_is_one_launch(fake):
         ok(L.stein_icp_proposal_mmd(x, y, B, K, 1, sigma, out, None))
         assert len(names()) == 1, names()
     """)
+
+
+def test_which_contexts_build_an_index(fake):
+    """Either side of the lines: few FP32 queries need more evaluations to
+    repay an index, unless normals come from it too; the screens do not."""
+    run(fake, """
+        def indexed(K, m, n_ref, **cfg):
+            rc, ctx = init(4000, n_ref, num_particles=K, batch_size=m, **cfg)
+            ok(rc)
+            F.fake_clear()
+            ok(L.stein_icp_step(ctx, 1, None))
+            L.stein_icp_destroy(ctx)
+            return ran("index_nn") == 1
+
+        for K, m, n_ref, fp32, plane, screen in (
+                (16, 32, 29000, False, False, False), (16, 32, 30000, False, True, True),
+                (16, 32, 58000, False, True, True), (16, 32, 59000, True, True, True),
+                (64, 32, 7400, False, True, True), (64, 32, 14700, True, True, True),
+                (64, 64, 3600, False, False, True), (64, 64, 3700, True, True, True)):
+            assert indexed(K, m, n_ref) == fp32, (K, m, n_ref)
+            assert indexed(K, m, n_ref, metric=S.METRIC_PLANE) == plane, (K, m, n_ref)
+            for mode in (S.NN_BF16_RERANK, S.NN_F16_RERANK):
+                assert indexed(K, m, n_ref, nn_mode=mode) == screen, (K, m, n_ref)
+    """)
