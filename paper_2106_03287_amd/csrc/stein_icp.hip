@@ -152,10 +152,15 @@ bool index_launches(int lanes, int64_t nq) { return lanes * nq <= ((int64_t)1 <<
 // Lanes per query of the indexed search. Few queries leave the chip to a few
 // wavefronts, whose dependent steps bound the launch: with 16 lanes a
 // wavefront waits for the longest of 4 queries, with 4 of 16. Many queries are
-// bound by the instructions, of which 4 lanes take fewer. 30,000 queries run
-// 25 % faster with 16 lanes, 300,000 26 % faster with 4 (figures at
-// index_nn_kernel).
-int default_index_lanes(int64_t queries) { return queries >= 131072 ? 4 : 16; }
+// bound by the instructions, of which 4 lanes take fewer. us an iteration of
+// 100 particles, 4 / 16 lanes, the first 25 iterations and from the 75th on:
+// 30,000 queries, tabletop (20,000 references) 44 / 40 and 31.6 / 27.5, street
+// (100,000) 86 / 68 and 38.2 / 34.4; 45,000 47 / 50 and 32.7 / 33.5, 90 / 79 and
+// 40.1 / 41.7; 60,000 48 / 56 and 35.5 / 39.0, 93 / 87 and 44.1 / 49.2; 100,000
+// 61 / 79 and 43.7 / 53.4, 112 / 118 and 54.7 / 68.2; 200,000 94 / 134 and 69.7 /
+// 95.5, 149 / 186 and 80.5 / 115.9. Whole stand-alone searches of 20,000 to
+// 60,000 queries are the same within 3 %, of 130,000 4 to 8 % faster with 4.
+int default_index_lanes(int64_t queries) { return queries >= 49152 ? 4 : 16; }
 
 Tiling default_tiling(const std::vector<PairDesc>& pd, int64_t nq)
 {

@@ -319,3 +319,26 @@ def test_which_contexts_build_an_index(fake):
             for mode in (S.NN_BF16_RERANK, S.NN_F16_RERANK):
                 assert indexed(K, m, n_ref, nn_mode=mode) == screen, (K, m, n_ref)
     """)
+
+
+def test_lanes_of_an_indexed_search(fake):
+    """Either side of the line, for a context (all its pairs together) and for a
+    stand-alone search."""
+    run(fake, """
+        def lanes(found):
+            assert found == 1
+            return 4 if ran("index_nn_kernelILi4") else 16
+
+        for pairs, K, m, want in ((1, 100, 491, 16), (1, 100, 492, 4), (3, 100, 163, 16), (3, 100, 164, 4)):
+            rc, ctx = init(500, 20000, pairs=pairs, num_particles=K, batch_size=m)
+            ok(rc)
+            F.fake_clear()
+            ok(L.stein_icp_step(ctx, 1, None))
+            assert lanes(ran("index_nn")) == want, (pairs, K, m)
+            L.stein_icp_destroy(ctx)
+        ref = malloc(12 * 20000)
+        for nq, want in ((49151, 16), (49152, 4)):
+            F.fake_clear()
+            ok(L.stein_icp_nn(malloc(12 * nq), nq, ref, 20000, S.NN_FP32, malloc(4 * nq), None, None))
+            assert lanes(ran("index_nn")) == want, nq
+    """)
