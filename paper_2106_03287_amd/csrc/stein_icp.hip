@@ -993,6 +993,8 @@ int run_knn(const float4* q4, int64_t nq, const float4* ref4, int64_t n_ref, int
     return STEIN_ICP_OK;
 }
 
+static_assert(kKnnMax <= kCoincident, "the index finds so many coincident references");
+
 // Normals of an indexed cloud's references (nrm: 4 doubles per reference), on
 // the stream. lists: scratch of 8 d.n k bytes.
 hipError_t enqueue_index_normals(const IndexDesc& d, const IndexDesc* d_desc, const float4* nodes, const float4* ref4,
