@@ -1200,7 +1200,8 @@ int run_indexed_nn(const char* fn, IndexedNn& n, const float* q_xyz, int64_t nq,
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(&flag, n.flag, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const hipError_t waited = hipStreamSynchronize(s);   // also after an error: the plan's upload may still read `blob`
+    if (e == hipSuccess) e = waited;
     if (e == hipSuccess && flag) return fail(STEIN_ICP_E_INVALID, "a coordinate is non-finite or above 1e9");
     if (e == hipSuccess) {
         hipLaunchKernelGGL(nn_finish_kernel, grid1d(nq, 256), dim3(256), 0, s, n.keys, n.q4, n.r4, n_ref, nq, 1, 1, idx,

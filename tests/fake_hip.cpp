@@ -37,6 +37,7 @@ struct Failure {
 };
 std::map<std::string, Failure> g_fail;
 uint64_t g_blocks = 0;
+bool g_in_flight = false;   // a copy since the last wait
 int g_last = kOk;
 int g_device = 0;
 std::map<void*, int> g_stream_device;
@@ -108,6 +109,7 @@ int fake_launches() { return (int)g_log.size(); }
 const char* fake_name(int i) { return g_log[i].name; }
 uint64_t fake_threads(int i, int d) { return (uint64_t)g_log[i].grid[d] * g_log[i].block[d]; }
 uint64_t fake_arg(int i, int w) { return g_log[i].arg[w]; }
+int fake_in_flight() { return g_in_flight; }
 int fake_is_device(uint64_t p) { return find((void*)p) != g_mem.end(); }
 void fake_device(int d) { g_device = d; }
 void fake_stream_device(void* s, int d) { g_stream_device[s] = d; }
@@ -142,6 +144,7 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*)
     if (injected("hipMemcpyAsync")) return done(kInjected);
     if (!fits(d, n) || !fits(s, n)) return done(kInvalidValue);
     std::memmove(d, s, n);
+    g_in_flight = true;
     return kOk;
 }
 int hipMemcpy(void* d, const void* s, size_t n, int k) { return hipMemcpyAsync(d, s, n, k, nullptr); }
@@ -219,7 +222,11 @@ int hipEventElapsedTime(float* ms, void* a, void* b)
 
 int hipStreamCreateWithFlags(void** s, unsigned) { *s = std::malloc(8); return kOk; }
 int hipStreamDestroy(void* s) { std::free(s); return kOk; }
-int hipStreamSynchronize(void*) { return kOk; }
+int hipStreamSynchronize(void*)
+{
+    g_in_flight = false;
+    return kOk;
+}
 int hipStreamIsCapturing(void*, int* st) { *st = 0; return kOk; }
 int hipStreamGetDevice(void* s, int* d)
 {

@@ -342,3 +342,24 @@ def test_lanes_of_an_indexed_search(fake):
             ok(L.stein_icp_nn(malloc(12 * nq), nq, ref, 20000, S.NN_FP32, malloc(4 * nq), None, None))
             assert lanes(ran("index_nn")) == want, nq
     """)
+
+
+def test_a_failed_indexed_search_waits_for_its_uploads(fake):
+    """Whichever launch of a stand-alone search's index fails, the call returns
+    only after the copy of the build's plan from its own host memory."""
+    run(fake, """
+        nq, n_ref = 100000, 100000
+        q, ref, idx = malloc(12 * nq), malloc(12 * n_ref), malloc(4 * nq)
+        for call in (L.stein_icp_nn, L.stein_icp_nn_noalloc):
+            failed = 0
+            for nth in range(1, 30):
+                F.fake_clear()
+                F.fake_fail(b"hipLaunchKernel", nth, 1)
+                rc = call(q, nq, ref, n_ref, S.NN_FP32, idx, None, None)
+                F.fake_no_failures()
+                assert not F.fake_in_flight(), nth
+                if rc == 0:
+                    break
+                failed += 1
+            assert failed >= 8 and ran("index_nn") == 1
+    """)
