@@ -39,6 +39,7 @@ SCREENS = ("bf16", "f16")
 NN_MODE = {"fp32": 0, "bf16": 1, "f16": 2}     # STEIN_ICP_NN_*
 DTYPE = {"fp32": "f32", "bf16": "bf16+f32", "f16": "f16+f32"}
 NN_SOURCES = ["paper_2106_03287_amd/csrc/nn.hpp", "paper_2106_03287_amd/csrc/common.hpp"]
+INDEX_SOURCES = ["paper_2106_03287_amd/csrc/ref_index.hpp", "paper_2106_03287_amd/csrc/common.hpp"]
 NN_BF16_SOURCES = NN_SOURCES + ["paper_2106_03287_amd/csrc/nn_bf16.hpp"]
 
 
@@ -97,9 +98,10 @@ def code_text(path):
 
 
 def nn_source_sha(nn="fp32"):
+    """Fingerprint of a search's kernel source; nn: its mode, or "index"."""
     import hashlib
     h = hashlib.sha256()
-    for f in (NN_BF16_SOURCES if nn in SCREENS else NN_SOURCES):
+    for f in (INDEX_SOURCES if nn == "index" else NN_BF16_SOURCES if nn in SCREENS else NN_SOURCES):
         h.update(code_text(os.path.join(ROOT, f)).encode())
     return h.hexdigest()[:16]
 
@@ -107,13 +109,14 @@ def nn_source_sha(nn="fp32"):
 def measured_counters(workload, tiling, nn="fp32"):
     """Counter figures of the NN kernel from the committed rocprofv3 runs
     (HBM bytes per launch from FETCH_SIZE / WRITE_SIZE scaled by a plain
-    copy, and the matrix-core busy fraction), if they were taken on the
-    current kernel source, this workload, search mode and NN shape; else {}."""
+    copy, and the busy fractions), if they were taken on the current kernel
+    source, this workload, search mode and NN shape (none for the indexed
+    search, mode "index"); else {}."""
     path = os.path.join(ROOT, "profiles", "nn_traffic.json")
     if not os.path.exists(path):
         return {}
     rec = json.load(open(path)).get(workload if nn == "fp32" else f"{workload}:{nn}")
-    shape = "%d,%d,%d,%d" % (tiling["queries_per_lane"], tiling["waves"], tiling["chunk"], tiling["persist"])
+    shape = tiling and "%d,%d,%d,%d" % (tiling["queries_per_lane"], tiling["waves"], tiling["chunk"], tiling["persist"])
     if not rec or rec.get("source_sha") != nn_source_sha(nn) or rec.get("tiling") != shape:
         return {}
     return rec
@@ -130,19 +133,22 @@ def measure_ceilings():
     return {k: (round(v, 1) if isinstance(v, float) else v) for k, v in CEILINGS.items()}
 
 
-def index_roofline(queries, refs, nn_ms):
+def index_roofline(queries, refs, nn_ms, counters):
     """The indexed search of a launch: the distances a balanced search cannot do
     without, 8 flops a level and query over log2(refs) levels, on the FP32
-    vector units; the rate of brute-force pair evaluations it stands for
-    beside it. refs: references of each query's cloud, weighted by queries."""
+    vector units; how busy these are with all that the search takes besides,
+    and the counted HBM bytes and their rate beside it. refs: references of each
+    query's cloud, weighted by queries."""
     t = nn_ms * 1e-3
     flops = sum(n * FLOPS_PER_PAIR * max(1, math.ceil(math.log2(r))) for n, r in zip(queries, refs))
     useful = flops / t / 1e12
-    pairs = sum(n * r for n, r in zip(queries, refs))
+    traffic = counters.get("hbm_bytes_per_launch")
     out = {"bound": "alu", "achieved": round(useful, 3), "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
-           "frac": round(useful / VALU_PEAK_TFLOPS, 4), "traffic": None, "avg_launch_ms": round(nn_ms, 5),
-           "flops_per_launch": flops, "kernel": "index_nn_kernel",
-           "brute_force_pair_evals_per_s": round(pairs / t, 1)}
+           "frac": round(useful / VALU_PEAK_TFLOPS, 4), "traffic": traffic, "avg_launch_ms": round(nn_ms, 5),
+           "flops_per_launch": flops, "kernel": "index_nn_kernel", "queries_per_s": round(sum(queries) / t, 1),
+           "hbm_gbps": None if traffic is None else round(traffic / t / 1e9, 1),
+           "hbm_frac": None if traffic is None else round(traffic / t / 1e9 / HBM_PEAK_GBPS, 4),
+           "valu_issue": counters.get("valu_issue"), "load_path_busy": counters.get("load_path_busy")}
     if CEILINGS:
         out["measured_peak"] = {"value": round(CEILINGS["fp32_fma_tflops"], 1), "unit": "TFLOP/s",
                                 "probe": "fp32_fma_tflops", "frac": round(useful / CEILINGS["fp32_fma_tflops"], 4)}
@@ -351,8 +357,8 @@ def main():
     ap.add_argument("--no-smi", action="store_true",
                     help="do not query rocm-smi (a profiler that initialises the GPU before the program starts "
                          "forbids starting another program)")
-    ap.add_argument("--autotune", type=int, default=0,
-                    help="(kept; without --tiling the context always tunes its search at init)")
+    ap.add_argument("--autotune", type=int, default=1,
+                    help="0: without --tiling, the context's default search shape instead of one tuned at init")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="run one plain device copy of this size first (counter calibration)")
     ap.add_argument("--iters", type=int, default=0,
@@ -384,8 +390,6 @@ def main():
         args.nn = AUTO_NN.get(args.workload, "fp32")
     if args.tiling == "pinned":   # the brute-force search of the mode in its best shape
         args.tiling = PINNED_TILING[(args.workload, args.nn)]
-    if not args.tiling:           # the context's own search: the index on every workload here
-        args.autotune = 1
     if args.copy_probe_mib:
         n = args.copy_probe_mib * (1 << 20) // 4
         a = torch.ones(n, dtype=torch.float32, device="cuda")
@@ -458,7 +462,8 @@ def main():
     nn_ms = sol.time_nn(max(20, min(200, int(200 / max(stage["nn"] / prob.T, 1e-3)))))
     pairs_per_launch = prob.K * prob.m * M
     roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters(prob.name, tiling, args.nn))
-                if args.tiling else index_roofline([prob.K * prob.m], [M], nn_ms))
+                if args.tiling else index_roofline([prob.K * prob.m], [M], nn_ms,
+                                                   measured_counters(prob.name, None, "index")))
     mismatch, identical = None, None
     if args.nn in SCREENS:
         # against the brute-force FP32 search from the same state: the first iteration's
@@ -497,14 +502,15 @@ def main():
                    "N": len(prob.pair.src), "M": M, "nn": args.nn, "metric": args.metric,
                    "step": "one full solve of T iterations"},
         "nn_queries_per_s": round(queries_per_s, 1),
-        "pair_evals_per_s": round(queries_per_s * M, 1),
+        # the indexed search does not evaluate them
+        "pair_evals_per_s": round(queries_per_s * M, 1) if args.tiling else None,
         "stage_ms_per_iter": {k: round(v / prob.T, 5) for k, v in stage.items()},
         "init_ms": round(init_ms, 2),
         "normals_ms": None if normals_ms is None else round(normals_ms, 3),
         "nn_tiling": tiling,
         "nn_mismatch_vs_fp32": mismatch,
         "particles_identical_to_fp32_solve": identical,
-        "nn_source_sha": nn_source_sha(args.nn),
+        "nn_source_sha": nn_source_sha(args.nn if args.tiling else "index"),
         "torch": torch.__version__,
         "roofline": roofline,
     }
@@ -576,7 +582,8 @@ def run_batched(args):
     nn_ms = batch.time_nn(20)
     pairs_per_launch = sum(K * m * len(p.pair.ref) for p in probs)
     roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters("batched", tiling, args.nn))
-                if args.tiling else index_roofline([K * m] * P, [len(p.pair.ref) for p in probs], nn_ms))
+                if args.tiling else index_roofline([K * m] * P, [len(p.pair.ref) for p in probs], nn_ms,
+                                                measured_counters("batched", None, "index")))
     value = P * T / (ms_b / 1e3)
     out = {
         "metric": METRIC,
@@ -637,7 +644,7 @@ def run_mc(args):
     cfg = S.stein_icp_default_config(num_particles=1, batch_size=prob.m, schedule_rows=T, lr=prob.lr,
                                      seed=synth.MC_SEED, init_half_trans=synth.MC_HALF_TRANS,
                                      init_half_rot=synth.MC_HALF_ROT, nn_mode=nn_mode,
-                                     autotune=0 if args.tiling else 1)
+                                     autotune=0 if args.tiling else args.autotune)
     t_init = time.perf_counter()
     mc = S.SteinICP.batch(cfg, [src] * R, [ref] * R)      # library-drawn starts and minibatches
     init_ms = (time.perf_counter() - t_init) * 1e3
@@ -689,7 +696,7 @@ def run_mc(args):
     M = len(prob.pair.ref)
     pairs_per_launch = R * prob.m * M
     roofline = (nn_roofline(nn, pairs_per_launch, nn_ms, measured_counters("mc", tiling, nn))
-                if args.tiling else index_roofline([R * prob.m], [M], nn_ms))
+                if args.tiling else index_roofline([R * prob.m], [M], nn_ms, measured_counters("mc", None, "index")))
     r4 = lambda v: [round(float(x), 4) for x in v]  # noqa: E731
     out = {
         "metric": METRIC,

@@ -59,9 +59,10 @@ extern "C" {
  * carries in two parts what BF16 needs three for): one matrix product per
  * block of references instead of two, with an error bound of the same size.
  * All three modes return the same answers. A context whose searches repay it
- * indexes its references at init (clouds up to 2^24 points) and then searches
- * the index, in every mode and with the same answers, unless
- * stein_icp_set_nn_tiling asks for the mode's brute-force search. */
+ * indexes its references at init (clouds up to 2^24 points, fewer than 2^30
+ * queries a pair, and where the memory is there) and then searches the index,
+ * in every mode and with the same answers, unless stein_icp_set_nn_tiling asks
+ * for the mode's brute-force search. */
 enum { STEIN_ICP_NN_FP32 = 0, STEIN_ICP_NN_BF16_RERANK = 1, STEIN_ICP_NN_F16_RERANK = 2 };
 /* Update rule: Adam on -phi (Sec. V), or theta += lr * phi (Eq. 12). */
 enum { STEIN_ICP_OPT_ADAM = 0, STEIN_ICP_OPT_SGD = 1 };
@@ -212,7 +213,9 @@ int stein_icp_nn_tiling(const stein_icp_ctx *ctx, int32_t *queries_per_lane, int
  * BF16 screen takes 1 or 2 queries per lane, and 4 or 8 waves with 2. The
  * shape changes only how the search is split over workgroups, never its
  * result. Blocking (reallocates the per-chunk key buffer and synchronises
- * `hip_stream`). */
+ * `hip_stream`). A shape that does not fit the memory is refused
+ * (STEIN_ICP_E_NOMEM) and the one before stays; should even its buffers not be
+ * had again, steps are refused with the same code until a shape fits. */
 int stein_icp_set_nn_tiling(stein_icp_ctx *ctx, int32_t queries_per_lane, int32_t waves,
                             int32_t chunk, int32_t persist, void *hip_stream);
 

@@ -481,7 +481,7 @@ __global__ __launch_bounds__(kSplitThreads) void index_split_kernel(IndexBuildAr
 // longest side and quartered, down to leaves of kFan slots. The sort counts
 // into s bins of equal width: points of a bin keep any order, which only
 // loosens a box where a quarter ends inside a bin. Bound by the latency of
-// its four passes over LDS: 24 us, also for many chunks (a bitonic sort of
+// its four passes over LDS: 25 us, also for many chunks (a bitonic sort of
 // keys of 20 bits of the coordinate took 53 us for 2,048 slots and 77 for
 // 4,096).
 // References that coincide (the zeros of a scanner's empty returns) fill leaves
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kSplitThreads) void index_split_kernel(IndexBuildAr
 // the others get empty boxes: their points are found in no search. 100,000
 // queries of 100,000 street references, 30 % of both zero: 72 us a launch,
 // 2,798 with every leaf visited (1,446 by brute force in FP32); all zero 132,
-// 15,263 and 1,301. The launch itself costs the same without them.
+// 15,263 and 1,301. To look for such leaves takes about 1 us of the launch.
 __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildArgs a)
 {
     __shared__ float xyz[3][kChunk];
@@ -835,19 +835,25 @@ inline int pair_distance_blocks(int K, int threads) { return (2 * K * kWave + th
 // queries are ordered by minibatch point, then particle, so that those of a
 // wavefront look for (nearly) the same place and read the same blocks.
 //
-// Many queries are bound by the issue of their loads (a 16-byte load of a
-// wavefront takes 16 cycles of the compute unit's load path; 4 lanes a query
-// take the fewest), few ones by the latency of the dependent steps, 5 (2,000
-// references) to 8 (100,000) a query; the whole index stays in L2. us a launch
-// with 4 and with 16 lanes (what it replaced: the brute-force search of the
-// mode): 300,000 queries of 100,000 street references 56 and 85 (1,055), 64
-// uneven pairs of 30,000 queries 284 and 506 (1,114), 1,000 runs of 300
-// queries of 20,000 60 and 80 (231), 30,000 of 20,000 tabletop 17.4 and 13.9
-// (34), 16,247 of 12,345 13.1 and 10.2 (85), 10,000 of 2,000 11.8 and 9.1
-// (9.9). Left out after measuring: upper levels staged in LDS (street +0 to
-// 7 %, tabletop +4 %, 64 pairs -1 %: their loads are few), several queries in
-// turn per group (street 72 -> 82), fan-out 64 on 16 lanes (tabletop 16.6,
-// street 112) and 4 on one lane (41, 94).
+// Many queries are bound by the vector units and the load path at once: 64
+// uneven pairs of 30,000 queries have the returns of their loads busy for 92 %
+// of the launch, and a vector instruction every 3.6 cycles of a SIMD, with 46 %
+// of the lanes active (102 to 111 vector instructions a query; a wavefront's 70
+// to 76 loads hit the L1 nine times in ten). 300,000 queries keep both at two
+// thirds to three quarters; few queries wait for the dependent steps, 5 (2,000
+// references) to 8 (100,000) a query. The index stays in the caches: 42 MB a
+// launch come from HBM for the street, 11 for the 1,000 runs. us a launch, the
+// first five / the middle / the last of a solve with 4 lanes, and with 16 at
+// its start (what the search replaced: the mode's brute-force one): 300,000
+// queries of 100,000 street references 159 / 65 / 58, 210 (1,055); 64 uneven
+// pairs of 30,000 queries 333 / 306 / 290, 603 (1,114); 1,000 runs of 300
+// queries of 20,000 67 / 65 / 65, 99 (231). From the 75th iteration on, 4 and
+// 16 lanes: 30,000 queries of 20,000 tabletop references 17.0 and 14.4 (34),
+// 100,000 22.9 and 31.8; 30,000 of 100,000 street references 22.6 and 20.1,
+// 100,000 29.7 and 42.6. Left out after measuring: upper levels staged in LDS
+// (street +0 to 7 %, tabletop +4 %, 64 pairs -1 %: their loads are few), several
+// queries in turn per group (street 72 -> 82), fan-out 64 on 16 lanes (tabletop
+// 16.6, street 112) and 4 on one lane (41, 94).
 template <int L, bool BW>
 __global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_kernel(IndexSearchArgs a)
 {
@@ -875,7 +881,7 @@ __global__ __launch_bounds__(search_threads(L, BW), BW ? 8 : 1) void index_nn_ke
     const uint32_t fl = tid & (L - 1);
     if (tid < kIndexLevels) level_off[tid] = 4 * (int32_t)(d.level_off[tid] - d.level_off[0]);
     __syncthreads();
-    const uint32_t nq = (uint32_t)a.K * (uint32_t)a.m;   // at most 2^31
+    const uint32_t nq = (uint32_t)a.K * (uint32_t)a.m;   // below 2^30
     const uint32_t w = (uint32_t)wg * (T / L) + tid / L;
     if (w >= nq) return;   // whole groups; no barrier below
     const uint64_t qi = p * (uint64_t)nq + (uint64_t)(w % (uint32_t)a.K) * (uint32_t)a.m + w / (uint32_t)a.K;
@@ -977,7 +983,7 @@ struct IndexKnnArgs {
 // k smallest (distance, index) keys. grid ceil(slots / 16), 256 threads;
 // dynamic LDS index_nn_lds_bytes<16>(levels).
 // Bound like the search. Normals of a 20,000-point tabletop, k = 10, with the
-// covariances: 33 us (24 here) against 328 by brute force.
+// covariances: 31 us (22 here) against 328 by brute force.
 template <int R>
 __global__ __launch_bounds__(search_threads(16)) void index_knn_kernel(IndexKnnArgs a)
 {

@@ -253,10 +253,14 @@ bool const_bandwidth(const stein_icp_config& c)
 // bound keeps two search workgroups per compute unit.
 // Beside the indexed search the selection has 64 registers, so that two
 // workgroups of 1,024 threads share a compute unit, and spills some; up to
-// kBesideSearchK particles it still hides (K = 100: box 26.7 -> 25.5 us an
-// iteration, tabletop 32.3 -> 30.8, against distances beside the search and
-// selection beside the gradients, which is faster for more: K = 300, street
-// 121 -> 111).
+// kBesideSearchK particles it still hides. Where it stops to depends on what it
+// hides behind. us an iteration, distances beside the search and selection
+// beside the gradients / selection beside the search, minibatches of 100 and
+// 300: box (2,000 references) K = 100 23.0 / 22.7 and 25.5 / 24.5, 128 24.4 / 24.9
+// and 28.7 / 26.8, 160 26.5 / 29.3 and 32.9 / 31.3; tabletop 100 25.3 / 22.7 and
+// 28.4 / 27.1, 128 27.1 / 24.7 and 31.8 / 30.3, 160 28.9 / 28.8 and 35.8 / 32.9,
+// 256 37.1 / 42.4 and 48.4 / 44.8; street 128 30.6 / 27.8 and 36.4 / 37.0, 256
+// 40.8 / 41.6 and 55.2 / 50.7. At 128 no minibatch loses more than 2 %.
 constexpr size_t kFusedBandwidthLds = 48 * 1024;
 constexpr int kBesideSearchK = 128;
 int g_num_cus = 256;   // compute units of the device, read at the first init
@@ -585,7 +589,6 @@ void launch_index_nn(int lanes, bool bw, int levels, int64_t nq, int64_t pairs, 
     }
 }
 
-// Queries of the coming iteration from the current poses and step count.
 // Arrays of the context to a caller's device memory. A copy is a launch of
 // its own (about 2 us on the device, 4 us of the caller): one kernel takes up to
 // four where together they are at most 1 MB (a step of 10 particles with its
@@ -656,6 +659,7 @@ hipError_t copy_out(const stein_icp_ctx* c, std::initializer_list<OutArray> arra
     return hipSuccess;
 }
 
+// Queries of the coming iteration from the current poses and step count.
 hipError_t enqueue_queries(const stein_icp_ctx* c, hipStream_t s)
 {
     hipLaunchKernelGGL(queries_kernel, dim3((unsigned)ceil_div(c->nq, 256), (unsigned)c->P), dim3(256), 0, s,
@@ -1063,7 +1067,7 @@ void drop_index(stein_icp_ctx* c)
 // 10,000 x 1,500 377 / 416 (1,605 / 1,584). The screens, kinect: 1,000 x 4,000
 // 336 / 336 (1,347 / 1,309), x 10,000 362 / 388 (1,441 / 1,488), 512 x 30,000
 // 434 / 408 (1,731 / 1,607), 2,048 x 2,000 399 / 387 (1,691 / 1,443). Normals
-// want every reference's neighbours (33 us from the index for 20,000, 328
+// want every reference's neighbours (31 us from the index for 20,000, 328
 // without), so point-to-plane keeps the lower line.
 bool index_pays(const stein_icp_config& c, const std::vector<PairDesc>& pairs)
 {
