@@ -226,6 +226,7 @@ struct stein_icp_ctx {
 
     WorkItem* d_work = nullptr;  // separate allocations: resized by the tuner
     uint64_t* partial = nullptr;
+    size_t work_bytes = 0, partial_bytes = 0;   // of these
 
     hipStream_t cap_stream = nullptr;   // graph capture
     std::map<int, hipGraphExec_t> graphs;   // key 2 * iterations + starting parity
@@ -485,45 +486,53 @@ int64_t partial_elems(const stein_icp_ctx* c)
     return n;
 }
 
-// Work table and search buffers of the context's shape. The new buffers are
-// allocated before the old ones go, or, where both do not fit, in their place:
-// a failure then leaves none, and the caller either restores the shape before
-// or leaves the context without (need_buffers). The indexed search has no work
-// table.
+// Work table and search buffers of the context's shape. Buffers of the same
+// sizes stay. Else the new ones are allocated before the old ones go, or, where
+// both do not fit, in their place: a failure then leaves none, and the caller
+// either restores the shape before or leaves the context without
+// (need_buffers). The indexed search has no work table.
 int upload_tiling(stein_icp_ctx* c, hipStream_t s)
 {
     build_work(c);
-    WorkItem* work = nullptr;
-    uint64_t* partial = nullptr;
-    auto alloc = [&] {
-        const size_t bytes = sizeof(WorkItem) * c->work.size();
-        if ((bytes == 0 || hipMalloc(&work, bytes) == hipSuccess) &&
-            hipMalloc(&partial, sizeof(uint64_t) * std::max<int64_t>(partial_elems(c), 1)) == hipSuccess)
-            return true;
-        (void)hipGetLastError();
-        if (work) (void)hipFree(work);
-        work = nullptr;
-        partial = nullptr;
-        return false;
-    };
-    const bool beside = alloc();
-    if (c->d_work) (void)hipFree(c->d_work);
-    if (c->partial) (void)hipFree(c->partial);
-    c->d_work = nullptr;
-    c->partial = nullptr;
-    for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);   // they hold the old buffers
-    c->graphs.clear();
-    if (!beside && !alloc()) return fail(STEIN_ICP_E_NOMEM, "device allocation of the NN work table failed");
-    c->d_work = work;
-    c->partial = partial;
+    const size_t work_bytes = sizeof(WorkItem) * c->work.size();
+    const size_t partial_bytes = sizeof(uint64_t) * std::max<int64_t>(partial_elems(c), 1);
+    if (c->partial && work_bytes == c->work_bytes && partial_bytes == c->partial_bytes) {
+        HIP_TRY(hipDeviceSynchronize());   // as hipFree does: launches of any stream may read the tables
+    } else {
+        WorkItem* work = nullptr;
+        uint64_t* partial = nullptr;
+        auto alloc = [&] {
+            if ((work_bytes == 0 || hipMalloc(&work, work_bytes) == hipSuccess) &&
+                hipMalloc(&partial, partial_bytes) == hipSuccess)
+                return true;
+            (void)hipGetLastError();
+            if (work) (void)hipFree(work);
+            work = nullptr;
+            partial = nullptr;
+            return false;
+        };
+        const bool beside = alloc();
+        if (c->d_work) (void)hipFree(c->d_work);
+        if (c->partial) (void)hipFree(c->partial);
+        c->d_work = nullptr;
+        c->partial = nullptr;
+        for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);   // they hold the old buffers
+        c->graphs.clear();
+        if (!beside && !alloc()) return fail(STEIN_ICP_E_NOMEM, "device allocation of the NN work table failed");
+        c->d_work = work;
+        c->partial = partial;
+        c->work_bytes = work_bytes;
+        c->partial_bytes = partial_bytes;
+    }
     HIP_TRY(hipMemcpyAsync(c->d_pairs, c->pairs.data(), sizeof(PairDesc) * c->P, hipMemcpyHostToDevice, s));
     if (!c->indexed) {
         HIP_TRY(hipMemcpyAsync(c->d_groups, c->groups.data(), sizeof(PairDesc) * c->groups.size(),
                                hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync(c->d_work, c->work.data(), sizeof(WorkItem) * c->work.size(), hipMemcpyHostToDevice,
-                               s));
+        HIP_TRY(hipMemcpyAsync(c->d_work, c->work.data(), work_bytes, hipMemcpyHostToDevice, s));
     }
     HIP_TRY(hipStreamSynchronize(s));
+    for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);   // of the shape before
+    c->graphs.clear();
     return STEIN_ICP_OK;
 }
 
