@@ -138,7 +138,8 @@ def index_roofline(queries, refs, nn_ms, counters):
     without, 8 flops a level and query over log2(refs) levels, on the FP32
     vector units; how busy these are with all that the search takes besides,
     and the counted HBM bytes and their rate beside it. refs: references of each
-    query's cloud, weighted by queries."""
+    query's cloud, weighted by queries. nn_ms: the mean of a solve's launches (the
+    early ones, of spread particles, take longer), as the counters'."""
     t = nn_ms * 1e-3
     flops = sum(n * FLOPS_PER_PAIR * max(1, math.ceil(math.log2(r))) for n, r in zip(queries, refs))
     useful = flops / t / 1e12
@@ -462,7 +463,7 @@ def main():
     nn_ms = sol.time_nn(max(20, min(200, int(200 / max(stage["nn"] / prob.T, 1e-3)))))
     pairs_per_launch = prob.K * prob.m * M
     roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters(prob.name, tiling, args.nn))
-                if args.tiling else index_roofline([prob.K * prob.m], [M], nn_ms,
+                if args.tiling else index_roofline([prob.K * prob.m], [M], stage["nn"] / prob.T,
                                                    measured_counters(prob.name, None, "index")))
     mismatch, identical = None, None
     if args.nn in SCREENS:
@@ -582,7 +583,7 @@ def run_batched(args):
     nn_ms = batch.time_nn(20)
     pairs_per_launch = sum(K * m * len(p.pair.ref) for p in probs)
     roofline = (nn_roofline(args.nn, pairs_per_launch, nn_ms, measured_counters("batched", tiling, args.nn))
-                if args.tiling else index_roofline([K * m] * P, [len(p.pair.ref) for p in probs], nn_ms,
+                if args.tiling else index_roofline([K * m] * P, [len(p.pair.ref) for p in probs], stage["nn"] / T,
                                                 measured_counters("batched", None, "index")))
     value = P * T / (ms_b / 1e3)
     out = {
@@ -696,7 +697,8 @@ def run_mc(args):
     M = len(prob.pair.ref)
     pairs_per_launch = R * prob.m * M
     roofline = (nn_roofline(nn, pairs_per_launch, nn_ms, measured_counters("mc", tiling, nn))
-                if args.tiling else index_roofline([R * prob.m], [M], nn_ms, measured_counters("mc", None, "index")))
+                if args.tiling else index_roofline([R * prob.m], [M], stage["nn"] / T,
+                                                   measured_counters("mc", None, "index")))
     r4 = lambda v: [round(float(x), 4) for x in v]  # noqa: E731
     out = {
         "metric": METRIC,
