@@ -489,9 +489,12 @@ __global__ __launch_bounds__(kSplitThreads) void index_split_kernel(IndexBuildAr
 // all: its bound excludes no tie. Of three such leaves and more in a row, the
 // first two take the kCoincident lowest indices, more than any answer holds, and
 // the others get empty boxes: their points are found in no search. 100,000
-// queries of 100,000 street references, 30 % of both zero: 72 us a launch,
-// 2,798 with every leaf visited (1,446 by brute force in FP32); all zero 132,
-// 15,263 and 1,301. To look for such leaves takes about 1 us of the launch.
+// queries of 100,000 street references, 30 % of both zero: 71 us a launch,
+// 2,798 with every leaf visited (1,436 by brute force in FP32); all zero 131,
+// 15,263 and 1,331. A wavefront takes a run of such leaves: one workgroup for
+// one run after another made a stand-alone search of a cloud of 492 such places
+// 506 us, 271 so and 266 without looking for them. To look takes about 1 us of
+// the launch.
 __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildArgs a)
 {
     __shared__ float xyz[3][kChunk];
@@ -508,9 +511,9 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
         hist[i] = 0;
         if (i < ch.n) {
             const float4 p = src[i];
-            xyz[0][i] = p.x;
-            xyz[1][i] = p.y;
-            xyz[2][i] = p.z;
+            xyz[0][i] = p.x + 0.f;   // -0 as 0: one place, and the same distances
+            xyz[1][i] = p.y + 0.f;
+            xyz[2][i] = p.z + 0.f;
             orig[i] = ch.from < 0 ? (uint32_t)i : __float_as_uint(p.w);
         }
     }
@@ -625,49 +628,86 @@ __global__ __launch_bounds__(kChunkThreads) void index_chunk_kernel(IndexBuildAr
     };
     const bool left_out = leaf >= 2 && same(leaf, leaf - 1) && same(leaf, leaf - 2);
     if (__syncthreads_or(left_out)) {
-        __shared__ uint32_t place[3];
-        for (int h = 0, end; h < kLeaves; h = end) {
-            for (end = h + 1; end < kLeaves && same(end, h);) ++end;
-            if (end - h < 3) continue;
-            const bool in = leaf >= h && leaf < end;
-            uint32_t pid[4], id[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                pid[u] = order[4 * tid + u];
-                id[u] = in && (int)pid[u] < ch.n ? orig[pid[u]] : kNoPoint;
+        __shared__ uint16_t run[kLeaves / 3], beyond[kChunkThreads / kWave][kCoincident];
+        __shared__ uint32_t few[kChunkThreads / kWave][kWave];
+        __shared__ int runs;
+        auto wave_fence = [] {   // between a wavefront's own LDS stores and loads
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        };
+        if (tid == 0) runs = 0;
+        __syncthreads();
+        if ((tid & 3) == 2 && left_out && !(leaf >= 3 && same(leaf, leaf - 3))) run[atomicAdd(&runs, 1)] = (uint16_t)(leaf - 2);
+        __syncthreads();
+        for (int r = wave; r < runs; r += kChunkThreads / kWave) {   // a wavefront per run
+            const int h = run[r];
+            int end = kLeaves;
+            for (int e0 = h + 3; e0 < end; e0 += kWave) {
+                const int e = e0 + lane;
+                const uint64_t other = __ballot(e < kLeaves && !same(e, h));
+                if (other) end = e0 + __builtin_ctzll(other);
             }
-            auto count = [&](uint32_t most) {   // points of the run with indices up to most
-                uint32_t c = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) c += (uint32_t)__builtin_popcountll(__ballot(id[u] <= most));
-                __syncthreads();
-                if (lane == 0) wsum[wave] = c;
-                __syncthreads();
-                c = 0;
-                for (int w = 0; w < kChunkThreads / kWave; ++w) c += wsum[w];
-                return c;
-            };
-            uint32_t lo = 0, hi = (uint32_t)kIndexMaxRef;   // the kCoincident-th lowest index
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) / 2;
-                if (count(mid) >= kCoincident) hi = mid;
-                else lo = mid + 1;
-            }
-            const uint32_t all = count(kNoPoint - 1);
-            if (tid == 0) {   // the lowest, the other points, padding
-                place[0] = 0;
-                place[1] = min(all, (uint32_t)kCoincident);
-                place[2] = all;
-            }
-            __syncthreads();
-            if (in)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int kind = id[u] <= hi ? 0 : (id[u] != kNoPoint ? 1 : 2);
-                    order[kFan * h + atomicAdd(&place[kind], 1u)] = (uint16_t)pid[u];
+            uint16_t* slot = order + kFan * h;
+            const int n = kFan * (end - h);
+            auto index = [&](int i) -> uint32_t { return i < n && slot[i] < ch.n ? orig[slot[i]] : kNoPoint; };
+            // the kCoincident-th lowest index, `low`: of a wavefront's values by
+            // bisection; that of the lanes' least indices bounds it, and the few
+            // up to the bound decide
+            auto nth = [&](uint32_t x, uint32_t hi) {
+                uint32_t lo = 0;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) / 2;
+                    if (__builtin_popcountll(__ballot(x <= mid)) >= kCoincident) hi = mid;
+                    else lo = mid + 1;
                 }
-            __syncthreads();
+                return hi;
+            };
+            uint32_t least = kNoPoint;
+#pragma unroll 4
+            for (int i = lane; i < n; i += kWave) least = min(least, index(i));
+            uint32_t low = nth(least, (uint32_t)d.n);
+            int c = 0;
+            for (int i = lane; i - lane < n; i += kWave) {
+                const uint32_t id = index(i);
+                const uint64_t m = __ballot(id <= low);
+                const int at = c + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+                if (id <= low && at < kWave) few[wave][at] = id;
+                c += __builtin_popcountll(m);
+            }
+            wave_fence();
+            if (c <= kWave) {
+                low = nth(lane < c ? few[wave][lane] : kNoPoint, low);
+            } else {   // lanes that hold many low indices: over all points
+                uint32_t lo = 0;
+                while (lo < low) {
+                    const uint32_t mid = (lo + low) / 2;
+                    c = 0;
+                    for (int i = lane; i - lane < n; i += kWave) c += __builtin_popcountll(__ballot(index(i) <= mid));
+                    if (c >= kCoincident) low = mid;
+                    else lo = mid + 1;
+                }
+            }
+            // the points up to it that lie beyond the first two leaves change
+            // places with the others in these
+            int b = 0;
+            for (int i = kCoincident + lane; i - lane < n; i += kWave) {
+                const bool in = index(i) <= low;
+                const uint64_t m = __ballot(in);
+                const int at = b + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+                if (in && at < kCoincident) beyond[wave][at] = (uint16_t)i;
+                b += __builtin_popcountll(m);
+            }
+            wave_fence();
+            const bool high = lane < kCoincident && index(lane) > low;
+            const int at = __builtin_popcountll(__ballot(high) & ((1ull << lane) - 1ull));
+            if (high && at < b) {
+                const int i = beyond[wave][at];
+                const uint16_t p = slot[lane];
+                slot[lane] = slot[i];
+                slot[i] = p;
+            }
         }
+        __syncthreads();
         leaf_box();
         if (left_out)
 #pragma unroll

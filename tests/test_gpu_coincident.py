@@ -24,11 +24,14 @@ def _cloud(n, places, rng):
     for i, count in enumerate(places):
         c[at[:count]] = np.round(rng.uniform(-2, 2, 3), 2) if i else 0.0
         at = at[count:]
+    zero = c == 0
+    c[zero] = np.where(rng.random(zero.sum()) < 0.5, -0.0, 0.0)   # one place all the same
     return c.astype(np.float32)
 
 
 CASES = [(600, (33, 47, 48, 49, 64)), (4096, (1000, 1000)), (4096, (4096,)), (3000, (2999,)), (9000, (8999,)),
-         (20000, (6000, 100, 40)), (70000, (35000, 20000)), (300, (300,)), (4097, (4000,))]
+         (20000, (6000, 100, 40)), (70000, (35000, 20000)), (300, (300,)), (4097, (4000,)),
+         (4096, (48,) * 85), (12000, (97,) * 120), (4096, (272,) * 15)]
 
 
 @pytest.mark.parametrize("n,places", CASES)
