@@ -885,9 +885,9 @@ inline int pair_distance_blocks(int K, int threads) { return (2 * K * kWave + th
 // launch come from HBM for the street, 11 for the 1,000 runs. us a launch, the
 // first five / the middle / the last of a solve with 4 lanes, and with 16 at
 // its start (what the search replaced: the mode's brute-force one): 300,000
-// queries of 100,000 street references 159 / 65 / 58, 210 (1,055); 64 uneven
-// pairs of 30,000 queries 333 / 306 / 290, 603 (1,114); 1,000 runs of 300
-// queries of 20,000 67 / 65 / 65, 99 (231). From the 75th iteration on, 4 and
+// queries of 100,000 street references 160 / 66 / 58, 212 (1,055); 64 uneven
+// pairs of 30,000 queries 335 / 305 / 290, 608 (1,114); 1,000 runs of 300
+// queries of 20,000 67 / 65 / 65, 98 (231). From the 75th iteration on, 4 and
 // 16 lanes: 30,000 queries of 20,000 tabletop references 17.0 and 14.4 (34),
 // 100,000 22.9 and 31.8; 30,000 of 100,000 street references 22.6 and 20.1,
 // 100,000 29.7 and 42.6. Left out after measuring: upper levels staged in LDS
